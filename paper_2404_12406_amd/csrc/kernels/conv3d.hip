@@ -198,11 +198,11 @@ size_t filter_bytes(int dtype, const Conv3dGeom &q) {
 }  // namespace
 
 size_t conv3d_fwd_workspace(int dtype, const Conv3dGeom &q) {
-    return fold_bytes(dtype, q) + filter_bytes(dtype, q) + al256(conv_fwd_workspace(dtype, q.g));
+    return fold_bytes(dtype, q) + filter_bytes(dtype, q) + (dtype == kBF16 ? al256(conv_fwd_workspace(dtype, q.g)) : 0);
 }
 
 size_t conv3d_dgrad_workspace(int dtype, const Conv3dGeom &q) {
-    return fold_bytes(dtype, q) + filter_bytes(dtype, q) + al256(conv_dgrad_workspace(dtype, q.g));
+    return fold_bytes(dtype, q) + filter_bytes(dtype, q) + (dtype == kBF16 ? al256(conv_dgrad_workspace(dtype, q.g)) : 0);
 }
 
 size_t conv3d_wgrad_workspace(int dtype, const Conv3dGeom &q, bool with_db) {
@@ -216,7 +216,7 @@ int launch_conv3d_fwd(int dtype, const Conv3dGeom &q, const void *u, const void 
     void *uf = p, *wc = p + fold_bytes(dtype, q), *rest = p + fold_bytes(dtype, q) + filter_bytes(dtype, q);
     int err = fold(dtype, q, u, uf, st);
     if (!err) err = regroup(dtype, q, w, wc, 1, st);
-    if (!err) err = launch_conv_fwd(dtype, q.g, uf, wc, bias, v, rest, stream);
+    if (!err) err = launch_conv_fwd(dtype, q.g, uf, wc, bias, v, dtype == kBF16 ? rest : nullptr, stream);
     return err;
 }
 
@@ -226,7 +226,7 @@ int launch_conv3d_dgrad(int dtype, const Conv3dGeom &q, const void *dv, const vo
     char *p = static_cast<char *>(ws);
     void *uf = p, *wc = p + fold_bytes(dtype, q), *rest = p + fold_bytes(dtype, q) + filter_bytes(dtype, q);
     int err = regroup(dtype, q, w, wc, 1, st);
-    if (!err) err = launch_conv_dgrad(dtype, q.g, dv, wc, nullptr, uf, rest, stream);
+    if (!err) err = launch_conv_dgrad(dtype, q.g, dv, wc, nullptr, uf, dtype == kBF16 ? rest : nullptr, stream);
     if (!err) err = unfold(dtype, q, uf, bias, du, st);
     return err;
 }

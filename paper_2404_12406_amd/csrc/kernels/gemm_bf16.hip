@@ -36,13 +36,13 @@
 #include <hip/hip_ext.h>
 
 #include "common.h"
+#include "lds_dma.h"
 #include "limits.h"
 #include "../device.h"
 
 namespace ms {
 namespace g2 {
 
-typedef __attribute__((address_space(3))) void lds_void_t;
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4i16 lds_v4i16_t;
 
@@ -92,59 +92,6 @@ __device__ __forceinline__ Phase make_phase(const ConvGeom &g, int z) {
     f.dw = (f.w0 + g.pw - f.fw) / g.sw;
     return f;
 }
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *p, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), (short)0, (int)bytes, 0x00020000);
-}
-
-// One 16-byte LDS-DMA load: lane l's 16 bytes from byte offset `off` of the
-// buffer land at lds + 16 l (M0 holds the wave's LDS base).
-//
-// Contractions with an M/N-contiguous operand (ASM = true) issue it through
-// inline assembly so that the compiler does not track it: for a pending
-// LDS-DMA load the compiler puts a wait for every outstanding vector-memory
-// operation in front of each transposing LDS read (ds_read_b64_tr_b16),
-// which drains all refill loads in flight at every slice.  The others keep
-// the builtin, whose loads the scheduler can spread between the MFMAs.
-// Ordering in the assembly form is the kernel's own:
-//  * completion: its vmcnt waits before each barrier;
-//  * a refill writes a stage no wave reads until after the next barrier, and
-//    a volatile asm statement never moves across the barrier;
-//  * block_sync() tells the compiler that LDS may have changed, so no LDS
-//    value read before a barrier is reused after it.
-// M0 is reserved by the compiler and no other instruction of these kernels
-// reads it.
-// (The offset is computed into a named value first: passing a conditional
-// expression straight into the builtin inside a kernel template makes the
-// host pass drop the kernel's launch stub.)
-template <bool ASM>
-__device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, char *lds, uint32_t off) {
-    if constexpr (ASM) {
-        const uint32_t base = (uint32_t)(uintptr_t)(lds_void_t *)lds;
-        asm volatile("s_mov_b32 m0, %1\n\tbuffer_load_dwordx4 %0, %2, 0 offen lds" ::"v"(off), "s"(base), "s"(r));
-    } else {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t *)lds, 16, off, 0, 0, 0);
-    }
-}
-
-// Workgroup barrier; with untracked LDS-DMA loads it is also a compiler-level
-// memory fence (the barrier builtin alone does not stop the compiler from
-// keeping LDS values across it).
-template <bool ASM>
-__device__ __forceinline__ void block_sync() {
-    if constexpr (ASM) __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_s_barrier();
-    if constexpr (ASM) __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
-
-// s_waitcnt with only vmcnt constrained (gfx9 encoding: vmcnt[3:0] | [15:14],
-// expcnt[6:4] = 7, lgkmcnt[11:8] = 15).
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-    static_assert(N >= 0 && N < 64, "vmcnt range");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
-__device__ __forceinline__ void wait_lgkm0() { __builtin_amdgcn_s_waitcnt(0xc07f); }
 
 // 16-byte chunk swizzle of a K-contiguous tile row (128 bytes = 8 chunks).
 // 16 consecutive rows reading the same logical chunk land on 16 distinct

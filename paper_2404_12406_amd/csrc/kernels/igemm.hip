@@ -43,6 +43,16 @@ size_t wgrad_workspace(const ConvGeom &g, bool with_db);
 int conv_wgrad(const ConvGeom &g, const void *dy, const void *x, void *dw, void *db, void *ws, hipStream_t st);
 }  // namespace g2
 
+// fp32 kernel (gemm_f32.hip); each returns -1 when an operand is too large
+// for its 32-bit byte offsets.
+namespace f32g {
+size_t fwd_workspace(const ConvGeom &g);
+size_t dgrad_workspace(const ConvGeom &g);
+int conv_fwd(const ConvGeom &g, const void *x, const void *w, const void *bias, void *y, void *ws, hipStream_t st);
+int conv_dgrad(const ConvGeom &g, const void *dy, const void *w, const void *bias, void *dx, void *ws, hipStream_t st);
+int conv_wgrad(const ConvGeom &g, const void *dy, const void *x, void *dw, void *ws, size_t cap, hipStream_t st);
+}  // namespace f32g
+
 enum Mode { kFwd = 0, kDgrad = 1, kWgrad = 2 };
 
 struct IgemmParams {
@@ -632,13 +642,16 @@ SplitPlan wgrad_split(int dtype, const ConvGeom &g) {
 }  // namespace
 
 size_t conv_fwd_workspace(int dtype, const ConvGeom &g) {
-    return dtype == kBF16 ? g2::fwd_workspace(g) : 0;
+    return dtype == kBF16 ? g2::fwd_workspace(g) : f32g::fwd_workspace(g);
 }
 
 int launch_conv_fwd(int dtype, const ConvGeom &g, const void *x, const void *w, const void *bias,
                     void *y, void *ws, void *stream) {
     if (dtype == kBF16) {
         const int r = g2::conv_fwd(g, x, w, bias, y, ws, (hipStream_t)stream);
+        if (r >= 0) return r;
+    } else {
+        const int r = f32g::conv_fwd(g, x, w, bias, y, ws, (hipStream_t)stream);
         if (r >= 0) return r;
     }
     IgemmParams prm{};
@@ -658,7 +671,7 @@ int launch_conv_fwd(int dtype, const ConvGeom &g, const void *x, const void *w, 
 }
 
 size_t conv_dgrad_workspace(int dtype, const ConvGeom &g, bool with_db) {
-    return dtype == kBF16 ? g2::dgrad_workspace(g, with_db) : 0;
+    return dtype == kBF16 ? g2::dgrad_workspace(g, with_db) : f32g::dgrad_workspace(g);
 }
 
 int launch_conv_dgrad(int dtype, const ConvGeom &g, const void *dy, const void *w, const void *bias,
@@ -666,6 +679,9 @@ int launch_conv_dgrad(int dtype, const ConvGeom &g, const void *dy, const void *
     if (db_done) *db_done = false;
     if (dtype == kBF16) {
         const int r = g2::conv_dgrad(g, dy, w, bias, dx, ws, (hipStream_t)stream, db, db_done);
+        if (r >= 0) return r;
+    } else {
+        const int r = f32g::conv_dgrad(g, dy, w, bias, dx, ws, (hipStream_t)stream);
         if (r >= 0) return r;
     }
     IgemmParams prm{};
@@ -704,6 +720,9 @@ int launch_conv_wgrad(int dtype, const ConvGeom &g, const void *dy, const void *
             *db_done = db != nullptr;
             return r;
         }
+    } else {
+        const int r = f32g::conv_wgrad(g, dy, x, dw, ws, conv_wgrad_workspace(dtype, g, false), st);
+        if (r >= 0) return r;
     }
     SplitPlan sp = wgrad_split(dtype, g);
     IgemmParams prm{};

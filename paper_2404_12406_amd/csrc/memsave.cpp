@@ -936,7 +936,16 @@ ms_status backward_impl(ms_record *r, const ms_tensor *grad_y, const ms_tensor *
     const size_t ow = stg && w_read ? sg.add(&r->W) : kNoStage;
     const size_t ogx = stg && grad_x ? sg.add(grad_x) : kNoStage;
     const size_t ogw = stg && grad_W && grad_W->ndim >= 2 ? sg.add(grad_W) : kNoStage;
-    const size_t kb = backward_workspace(pl, kernels);
+    size_t kb = backward_workspace(pl, kernels);
+    // an fp32 input gradient takes workspace only to split its reduction and
+    // runs unsplit without: so it does when the fixed scratch cannot hold both
+    // the stand-ins and its partials
+    bool dgrad_ws = true;
+    if (fixed_scratch && pl.dtype == MS_F32 && (kernels & MS_K_DGRAD) && sg.bytes + kb > ms::kScratchBytes &&
+        (pl.kind == MS_CONV2D || pl.kind == MS_LINEAR || pl.kind == MS_CONV_TRANSPOSE2D)) {
+        kb = backward_workspace(pl, kernels & ~(uint32_t)MS_K_DGRAD);
+        dgrad_ws = false;
+    }
     const size_t ws_bytes = sg.bytes + kb;
     char *base = nullptr;
     if (ws_bytes && fixed_scratch) {
@@ -968,7 +977,8 @@ ms_status backward_impl(ms_record *r, const ms_tensor *grad_y, const ms_tensor *
         bool db_done = false;
         void *db_dgrad = (kernels & MS_K_BGRAD) && !(kernels & MS_K_WGRAD) ? grad_b->data : nullptr;
         if (!err && (kernels & MS_K_DGRAD))
-            err = ms::launch_conv_dgrad(pl.dtype, pl.g, dy, wk, nullptr, gx, ws, stream, db_dgrad, &db_done);
+            err = ms::launch_conv_dgrad(pl.dtype, pl.g, dy, wk, nullptr, gx, dgrad_ws ? ws : nullptr, stream, db_dgrad,
+                                        &db_done);
         if (!err && (kernels & MS_K_WGRAD))
             err = ms::launch_conv_wgrad(pl.dtype, pl.g, dy, xk, gw, (kernels & MS_K_BGRAD) ? grad_b->data : nullptr, ws,
                                         stream, &db_done);
@@ -982,7 +992,8 @@ ms_status backward_impl(ms_record *r, const ms_tensor *grad_y, const ms_tensor *
         // input gradient is g's forward of grad_y; the weight gradient is g's
         // weight gradient with x as its output gradient and grad_y as its input
         bool db_unused = false;
-        if (kernels & MS_K_DGRAD) err = ms::launch_conv_fwd(pl.dtype, pl.g, dy, wk, nullptr, gx, ws, stream);
+        if (kernels & MS_K_DGRAD)
+            err = ms::launch_conv_fwd(pl.dtype, pl.g, dy, wk, nullptr, gx, dgrad_ws ? ws : nullptr, stream);
         if (!err && (kernels & MS_K_WGRAD))
             err = ms::launch_conv_wgrad(pl.dtype, pl.g, xk, dy, gw, nullptr, ws, stream, &db_unused);
         if (!err && (kernels & MS_K_BGRAD))

@@ -1,0 +1,107 @@
+"""The fp32 implicit GEMM at the edges of its tiles, loads and splits: ragged
+rows and columns of every tile, channel counts with and without whole
+vectors, reductions of whole steps in one tap and not, more taps than a
+tap mask holds, split and unsplit, strided phases with and without taps.
+
+Bar: with accumulators that run over at most 256 products and are then added
+up, every result is within (256 + K / 256 + 40) * 2^-24 of the sum of its
+products' magnitudes (K products; 40 bounds the split sums, the bias and the
+final rounding), which the oracle gives from the magnitudes of the operands."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2404_12406_amd as ms
+import synth
+
+from _gpu import dev, guarded_empty, guards_intact, host
+
+pytestmark = pytest.mark.gpu
+
+
+def _bar(k, magnitude):
+    return (256 + k / 256 + 40) * 2.0 ** -24 * magnitude
+
+
+def _within(name, got, ref, magnitude, k):
+    bad = np.abs(got - ref) - _bar(k, magnitude)
+    assert np.isfinite(got).all() and bad.max() <= 0, (name, float(np.abs(got - ref).max()), float(bad.max()))
+
+
+CONVS = [
+    # x shape, w shape, stride, pad
+    ((4225, 64), (1030, 64), None, None),                    # 128 x 128 tiles, ragged both ways, tap steps
+    ((4225, 66), (1030, 66), None, None),                    # the same size on 4-byte loads
+    ((70, 36), (9, 36), None, None),                         # vectors, but no whole step
+    ((33, 1), (1, 1), None, None),                           # one product, one column
+    ((2, 32, 17, 19), (33, 32, 3, 3), (1, 1), (1, 1)),       # forward by tap steps, gradients on 4-byte loads
+    ((2, 64, 15, 14), (96, 64, 3, 3), (2, 2), (1, 1)),       # strided: four phases by tap steps
+    ((2, 32, 9, 10), (32, 32, 1, 1), (2, 2), (0, 0)),        # phases that no tap reaches
+    ((1, 32, 6, 5), (32, 32, 6, 6), (1, 1), (3, 3)),         # 36 taps: more than a tap mask holds
+    ((1, 64, 1, 1), (32, 64, 3, 3), (1, 1), (1, 1)),         # every tap but one in the padding
+    ((1, 128, 4, 4), (256, 128, 3, 3), (1, 1), (1, 1)),      # a deep reduction of few tiles: split
+    ((9, 8, 40, 37), (8, 8, 3, 3), (1, 1), (1, 1)),          # few channels both ways
+    ((3, 20, 13, 11), (36, 20, 3, 2), (3, 2), (0, 1)),       # vectors across taps, uneven strides
+    ((2, 5, 12, 12), (7, 5, 5, 5), (2, 1), (2, 1)),          # odd channels
+    ((2, 3, 33, 30), (64, 3, 7, 7), (2, 2), (3, 3)),         # a stem
+]
+
+
+@pytest.mark.parametrize("case", range(len(CONVS)))
+def test_f32_contractions(case):
+    xs, ws, stride, pad = CONVS[case]
+    seed = 9000 + 10 * case
+    fan = int(np.prod(ws[1:]))
+    x = synth.normal(xs, seed, dtype="f32")
+    w = synth.kaiming_uniform(ws, seed + 1, fan, dtype="f32")
+    b = synth.normal((ws[0],), seed + 2, 1.0, dtype="f32")
+    if stride is None:
+        spec = ms.Linear()
+        f, dx, dw = oracle.linear_forward, lambda g, w: oracle.linear_input_grad(g, w), lambda g, x: oracle.linear_weight_grad(g, x)
+    else:
+        spec = ms.Conv2d(stride, pad)
+        f = lambda x, w, b: oracle.conv2d_forward(x, w, b, stride, pad)
+        dx = lambda g, w: oracle.conv2d_input_grad(g, w, xs, stride, pad)
+        dw = lambda g, x: oracle.conv2d_weight_grad(g, x, ws, stride, pad)
+    ref = f(x, w, b)
+    gy = synth.normal(ref.shape, seed + 3, dtype="f32")
+    X, W, B, G = (dev(t, "f32") for t in (x, w, b, gy))
+    bufs = [guarded_empty(s, "f32") for s in (ref.shape, xs, ws, (ws[0],))]
+    y, rec = ms.layer_forward(spec, X, W, B, 7, y=bufs[0][0])
+    gx, gw, gb = ms.layer_backward(rec, G, bufs[1][0], bufs[2][0], bufs[3][0])
+    torch.cuda.synchronize()
+    for _, buf, guard in bufs:
+        assert guards_intact(buf, guard)
+    ax, aw, ag = np.abs(x), np.abs(w), np.abs(gy)
+    pixels = gy.size // ws[0]
+    _within("y", host(y), ref, f(ax, aw, np.abs(b)), fan)
+    _within("dx", host(gx), dx(gy, w), dx(ag, aw), ws[0] * fan // ws[1])
+    _within("dW", host(gw), dw(gy, x), dw(ag, ax), pixels)
+
+
+def test_f32_transposed_convolution_bias_and_output_padding():
+    xs, ws, stride, pad, op = (2, 32, 5, 6), (32, 34, 4, 3), (2, 3), (1, 1), (1, 2)
+    x, w = synth.normal(xs, 9500, dtype="f32"), synth.kaiming_uniform(ws, 9501, 34 * 12, dtype="f32")
+    b = synth.normal((34,), 9502, 1.0, dtype="f32")
+    ref = oracle.convt2d_forward(x, w, b, stride, pad, op)
+    y, _ = ms.layer_forward(ms.ConvTranspose2d(stride, pad, op), dev(x, "f32"), dev(w, "f32"), dev(b, "f32"), 0)
+    _within("y", host(y), ref, oracle.convt2d_forward(np.abs(x), np.abs(w), np.abs(b), stride, pad, op), 32 * 12)
+
+
+@pytest.mark.parametrize("channels", [32, 6])
+def test_f32_nonfinite_input_reaches_its_outputs_only(channels):
+    """An infinite and a NaN pixel: outputs that read them are not finite (an
+    infinity stays one where it meets no zero weight), the rest are as without."""
+    xs, ws = (1, channels, 9, 9), (16, channels, 3, 3)
+    x, w = synth.normal(xs, 9600, dtype="f32"), synth.kaiming_uniform(ws, 9601, 9 * channels, dtype="f32")
+    clean = oracle.conv2d_forward(x, w, None, (1, 1), (1, 1))
+    bad = x.copy()
+    bad[0, 1, 2, 2], bad[0, 3, 6, 7] = np.inf, np.nan
+    y, _ = ms.layer_forward(ms.Conv2d(1, 1), dev(bad, "f32"), dev(w, "f32"), None, 0)
+    y = host(y)
+    hit = np.zeros((9, 9), bool)
+    hit[1:4, 1:4] = hit[5:8, 6:9] = True
+    assert np.isinf(y[0, :, 1:4, 1:4]).all() and np.isnan(y[0, :, 5:8, 6:9]).all()
+    _within("rest", np.where(hit, 0, y), np.where(hit, 0, clean),
+            oracle.conv2d_forward(np.abs(x), np.abs(w), None, (1, 1), (1, 1)), 9 * channels)
