@@ -44,6 +44,17 @@
 #include "../device.h"
 
 namespace ms {
+
+// convolutions of few channels (few_f32.hip)
+namespace few {
+bool fwd_applies(const ConvGeom &g, const void *x);
+bool dgrad_applies(const ConvGeom &g, const void *dy);
+bool wgrad_applies(const ConvGeom &g);
+int conv_fwd(const ConvGeom &g, const void *x, const void *w, const void *bias, void *y, hipStream_t st);
+int conv_dgrad(const ConvGeom &g, const void *dy, const void *w, const void *bias, void *dx, hipStream_t st);
+int wgrad_parts(const ConvGeom &g, const void *dy, const void *x, float *part, int64_t stride, int n, hipStream_t st);
+}  // namespace few
+
 namespace f32g {
 
 using g2::dma16s;
@@ -753,6 +764,7 @@ int conv_fwd(const ConvGeom &g, const void *x, const void *w, const void *bias, 
     a.a = (const float *)x; a.b = (const float *)w; a.g = g;
     a.M = g.N * g.P * g.Q; a.N = g.K; a.K = g.R * g.S * g.C;
     if (a.M == 0 || a.N == 0) return 0;
+    if (few::fwd_applies(g, x)) return few::conv_fwd(g, x, w, bias, y, st);
     Plan p = fwd_plan(g);
     if (p.splits > 1 && (!ws || !al16(ws))) p.splits = 1;
     return run<kFwd>(p, g.C % 4 == 0 && al16(x) && al16(w), a, 1, y_elems(g), (const float *)bias, (float *)y, ws, st);
@@ -766,6 +778,7 @@ int conv_dgrad(const ConvGeom &g, const void *dy, const void *w, const void *bia
     a.M = g.N * Hb * Wb; a.N = g.C;
     a.K = ((g.R + g.sh - 1) / g.sh) * ((g.S + g.sw - 1) / g.sw) * g.K;
     if (a.M == 0 || a.N == 0) return 0;
+    if (few::dgrad_applies(g, dy)) return few::conv_dgrad(g, dy, w, bias, dx, st);
     Plan p = dgrad_plan(g);
     if (p.splits > 1 && (!ws || !al16(ws))) p.splits = 1;
     return run<kDgrad>(p, g.K % 4 == 0 && g.C % 4 == 0 && al16(dy) && al16(w), a, g.sh * g.sw, x_elems(g),
@@ -779,6 +792,12 @@ int conv_wgrad(const ConvGeom &g, const void *dy, const void *x, void *dw, void 
     a.a = (const float *)dy; a.b = (const float *)x; a.g = g;
     a.M = g.K; a.N = g.R * g.S * g.C; a.K = g.N * g.P * g.Q;
     if (a.M == 0 || a.N == 0) return 0;
+    const int64_t row = part_stride(w_elems(g));
+    const int rows = (int)std::min<int64_t>(512, (int64_t)cap / (row * 4));   // two blocks a CU
+    if (rows >= 64 && few::wgrad_applies(g) && ws && al16(ws)) {
+        const int err = few::wgrad_parts(g, dy, x, static_cast<float *>(ws), row, rows, st);
+        return err ? err : reduce(static_cast<const float *>(ws), rows, w_elems(g), nullptr, 1, (float *)dw, st);
+    }
     const Plan p = wgrad_plan(g, (int64_t)cap);
     if (p.splits > 1 && (!ws || !al16(ws))) return (int)hipErrorInvalidValue;
     return run<kWgrad>(p, g.K % 4 == 0 && g.C % 4 == 0 && al16(dy) && al16(x), a, 1, w_elems(g), nullptr, (float *)dw, ws, st);

@@ -45,6 +45,13 @@ CONVS = [
     ((3, 20, 13, 11), (36, 20, 3, 2), (3, 2), (0, 1)),       # vectors across taps, uneven strides
     ((2, 5, 12, 12), (7, 5, 5, 5), (2, 1), (2, 1)),          # odd channels
     ((2, 3, 33, 30), (64, 3, 7, 7), (2, 2), (3, 3)),         # a stem
+    # few channels and pixels enough for the kernels of their own
+    ((9, 8, 101, 301), (8, 8, 3, 3), (1, 1), (1, 1)),        # every pass, ragged strips of rows and columns
+    ((5, 3, 211, 251), (5, 3, 3, 3), (1, 1), (1, 0)),        # three input channels; five filters
+    ((5, 4, 215, 251), (13, 4, 3, 2), (1, 2), (0, 1)),       # a column step of two, an even filter
+    ((5, 16, 131, 403), (16, 16, 3, 3), (1, 1), (2, 2)),     # sixteen both ways, wide padding
+    ((3, 1, 301, 301), (2, 1, 5, 5), (1, 1), (2, 2)),        # one channel, 5 x 5
+    ((16, 4, 257, 259), (24, 4, 7, 7), (2, 2), (3, 3)),      # strided phases of the input gradient
 ]
 
 
@@ -105,3 +112,19 @@ def test_f32_nonfinite_input_reaches_its_outputs_only(channels):
     assert np.isinf(y[0, :, 1:4, 1:4]).all() and np.isnan(y[0, :, 5:8, 6:9]).all()
     _within("rest", np.where(hit, 0, y), np.where(hit, 0, clean),
             oracle.conv2d_forward(np.abs(x), np.abs(w), None, (1, 1), (1, 1)), 9 * channels)
+
+
+def test_f32_few_channel_weight_gradient_keeps_infinities_apart():
+    """An infinity of one input channel reaches that channel's weight gradients
+    as an infinity, through ragged strips and ranges, and no other's."""
+    xs, ws = (4, 8, 61, 300), (8, 8, 3, 3)
+    x, gy = synth.normal(xs, 9700, dtype="f32"), synth.normal((4, 8, 61, 300), 9701, dtype="f32")
+    for pixel in ((0, 30, 299), (1, 60, 287), (3, 0, 0), (2, 31, 150)):
+        bad = x.copy()
+        bad[pixel[0], 5, pixel[1], pixel[2]] = np.inf
+        w = synth.kaiming_uniform(ws, 9702, 72, dtype="f32")
+        _, rec = ms.layer_forward(ms.Conv2d(1, 1), dev(bad, "f32"), dev(w, "f32"), None, 2)
+        _, gw, _ = ms.layer_backward(rec, dev(gy, "f32"))
+        gw = host(gw)
+        assert not np.isnan(gw).any() and np.isfinite(np.delete(gw, 5, 1)).all()
+        assert np.isinf(gw[:, 5, 1, 1]).all()
