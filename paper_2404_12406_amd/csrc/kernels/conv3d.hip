@@ -19,12 +19,32 @@
 //
 // The fold buffer is T / sd times the input; it lives in transient
 // workspace for one call.  The three kernels here are streaming passes.
+//
+// bf16 convolutions whose reduction step lies in one tap (channels a multiple
+// of 64, at most 32 taps; the input gradient at unit depth step; the weight
+// gradient for any whole vectors) do without: the depth taps are further taps
+// of the GEMM's loads (gemm_bf16.hip).  (8, 64, 16, 56, 56), 64 filters of
+// 3x3x3, us a pass with all its kernels, folded -> not: forward 216 -> 170, input
+// gradient 240 -> 155, weight gradient 243 -> 195; and the input gradient rounds
+// once (error 2.4e-3 -> 1.7e-3).  Their workspace stays the folded form's, which
+// tensors off 16-byte alignment take.
 #include <algorithm>
 
 #include "common.h"
 #include "../device.h"
 
 namespace ms {
+
+// bf16 without folding (gemm_bf16.hip); each returns -1 when it does not apply.
+namespace g2 {
+int conv3d_fwd(const Conv3dGeom &q, const void *u, const void *w, const void *bias, void *v, void *ws, size_t room,
+               hipStream_t st);
+int conv3d_dgrad(const Conv3dGeom &q, const void *dv, const void *w, const void *bias, void *du, void *ws, size_t room,
+                 hipStream_t st);
+int conv3d_wgrad(const Conv3dGeom &q, const void *dv, const void *u, void *dw, void *db, void *ws, size_t room,
+                 hipStream_t st);
+}  // namespace g2
+
 namespace {
 
 size_t al256(size_t n) { return (n + 255) / 256 * 256; }
@@ -212,6 +232,10 @@ size_t conv3d_wgrad_workspace(int dtype, const Conv3dGeom &q, bool with_db) {
 int launch_conv3d_fwd(int dtype, const Conv3dGeom &q, const void *u, const void *w, const void *bias, void *v,
                       void *ws, void *stream) {
     hipStream_t st = (hipStream_t)stream;
+    if (dtype == kBF16) {
+        const int r = g2::conv3d_fwd(q, u, w, bias, v, ws, conv3d_fwd_workspace(dtype, q), st);
+        if (r >= 0) return r;
+    }
     char *p = static_cast<char *>(ws);
     void *uf = p, *wc = p + fold_bytes(dtype, q), *rest = p + fold_bytes(dtype, q) + filter_bytes(dtype, q);
     int err = fold(dtype, q, u, uf, st);
@@ -223,6 +247,10 @@ int launch_conv3d_fwd(int dtype, const Conv3dGeom &q, const void *u, const void 
 int launch_conv3d_dgrad(int dtype, const Conv3dGeom &q, const void *dv, const void *w, const void *bias, void *du,
                         void *ws, void *stream) {
     hipStream_t st = (hipStream_t)stream;
+    if (dtype == kBF16) {
+        const int r = g2::conv3d_dgrad(q, dv, w, bias, du, ws, conv3d_dgrad_workspace(dtype, q), st);
+        if (r >= 0) return r;
+    }
     char *p = static_cast<char *>(ws);
     void *uf = p, *wc = p + fold_bytes(dtype, q), *rest = p + fold_bytes(dtype, q) + filter_bytes(dtype, q);
     int err = regroup(dtype, q, w, wc, 1, st);
@@ -234,6 +262,13 @@ int launch_conv3d_dgrad(int dtype, const Conv3dGeom &q, const void *dv, const vo
 int launch_conv3d_wgrad(int dtype, const Conv3dGeom &q, const void *dv, const void *u, void *dw, void *db, void *ws,
                         void *stream, bool *db_done) {
     hipStream_t st = (hipStream_t)stream;
+    if (dtype == kBF16) {
+        const int r = g2::conv3d_wgrad(q, dv, u, dw, db, ws, conv3d_wgrad_workspace(dtype, q, db != nullptr), st);
+        if (r >= 0) {
+            *db_done = db != nullptr;
+            return r;
+        }
+    }
     char *p = static_cast<char *>(ws);
     void *uf = p, *wc = p + fold_bytes(dtype, q), *rest = p + fold_bytes(dtype, q) + filter_bytes(dtype, q);
     int err = fold(dtype, q, u, uf, st);

@@ -72,6 +72,10 @@ struct Args {
                           // a column range of a wider output passes the full width
     int k_split, splits;  // reduction range per split (a multiple of BK) and split count
     uint32_t a_bytes, b_bytes;
+    // three-dimensional convolutions (D3): T depth taps; the images of the
+    // pixel side are m_depth per sample, image o reading A's (WGRAD: B's) tensor,
+    // a_depth images per sample, at depth o * d_step + d_off +- tap
+    int T, m_depth, a_depth, d_step, d_off;
 };
 
 struct Phase {
@@ -261,7 +265,8 @@ struct Cfg {
     static_assert(KG == 1 || (WR * WC) * (WM / 32) * (WN / 32) * 16 * 64 * 4 <= LDS_BYTES, "k-group partials fit LDS");
 };
 
-template <int MODE, int BM, int BN, int WR, int WC, int STAGES, int OCC, bool UNIT, int KG = 1, bool TS = false>
+template <int MODE, int BM, int BN, int WR, int WC, int STAGES, int OCC, bool UNIT, int KG = 1, bool TS = false,
+          bool D3 = false>
 __global__ __launch_bounds__(WR * WC * KG * 64, OCC) void gemm_kernel(const Args P) {
     __shared__ __attribute__((aligned(1024))) char smem[Cfg<MODE, BM, BN, WR, WC, STAGES, KG>::SMEM_BYTES];
     const int bx = (int)blockIdx.x, bz = (int)blockIdx.z;
@@ -272,6 +277,7 @@ __global__ __launch_bounds__(WR * WC * KG * 64, OCC) void gemm_kernel(const Args
 // LDS comes in from the kernel, which holds one arena for both tiles.
 template <int MODE, int BM, int BN, int WR, int WC, int STAGES, bool UNIT, int KG, bool TS>
 __device__ __forceinline__ void gemm_pair_block(const Args &P, char *smem, const int bx, const int bz) {
+    constexpr bool D3 = false;
 #include "gemm_block_body.inc"
 }
 
@@ -1280,12 +1286,13 @@ int64_t part_stride(int64_t elems) { return (elems + 3) / 4 * 4; }
 
 // The launch records the profiling events itself when its kind is armed, so
 // a pair spans this kernel's execution alone.
-template <int MODE, int BM, int BN, int WR, int WC, int STAGES, int OCC, bool UNIT, int KG = 1, bool TS = false>
+template <int MODE, int BM, int BN, int WR, int WC, int STAGES, int OCC, bool UNIT, int KG = 1, bool TS = false,
+          bool D3 = false>
 int go(const Args &a, dim3 grid, hipStream_t st) {
     const unsigned pk = MODE == kFwd ? kProfFwd : MODE == kWgrad ? kProfWgrad : kProfDgrad;
     void *eb = nullptr, *ee = nullptr;
     const bool timed = prof_pair(pk, &eb, &ee);
-    hipExtLaunchKernelGGL((gemm_kernel<MODE, BM, BN, WR, WC, STAGES, OCC, UNIT, KG, TS>), grid,
+    hipExtLaunchKernelGGL((gemm_kernel<MODE, BM, BN, WR, WC, STAGES, OCC, UNIT, KG, TS, D3>), grid,
                           dim3(WR * WC * KG * 64), 0, st, (hipEvent_t)eb, (hipEvent_t)ee, 0, a);
     const int err = (int)hipGetLastError();
     if (timed) prof_pair_done(pk, eb, ee, err == 0);
@@ -1544,12 +1551,12 @@ constexpr double kWgradRedUnits = 6.0;
 // 256 x 256 tile keeps the generic loads.
 constexpr bool kAutoWg[kNumTiles] = {false, true, false, true, false, true, false, false, false, false, false};
 
-Tile pick_conv_wgrad(long M, long N, long K, int splits_allowed, int *splits_out) {
+Tile pick_conv_wgrad(long M, long N, long K, int splits_allowed, int *splits_out, bool any_tile = false) {
     const int z = 1;
     double best = 1e300;
     Tile bt = kTiles[0];
     int bs = 1;
-    int forced = forced_tile();
+    int forced = any_tile ? -1 : forced_tile();
     // no k-group or narrow weight gradient: plan as usual
     if (forced >= 0 && (kTiles[forced].kg > 1 || kc_only(kTiles[forced]))) forced = -1;
     for (int ti = 0; ti < kNumTiles; ++ti) {
@@ -2173,6 +2180,234 @@ int conv_wgrad(const ConvGeom &g, const void *dy, const void *x, void *dw, void 
         const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>((n / 4 + 255) / 256, 2048));
         hipLaunchKernelGGL(reduce_kernel, dim3(blocks), dim3(256), 0, st, (const float *)a.part, p.splits, n, n,
                            (bf16 *)dw, (const float *)a.dbpart, db ? a.M : 0, (bf16 *)db, (const bf16 *)nullptr, 1);
+        err = (int)hipGetLastError();
+    }
+    return err;
+}
+
+// ---------------------------------------------------------------- three dimensions
+// A 3-D convolution with its depth taps as further taps of the tap-step (pixel-
+// step) loads: the taps (z, r, s) of one channel block are one reduction step
+// in the filter's own order [K][T][R][S][C], and a pixel's images are the
+// depths o of its sample.  Folding the depth into the channels instead
+// (conv3d.hip, with the figures of both) writes and reads T copies of the input.
+
+namespace {
+
+// tiles built for it: the forward and the input gradient's wide, ordinary and
+// 64-column ones; the weight gradient's ordinary ones and, for up to 64 filters,
+// 64 rows
+constexpr Tile kTiles3[] = {
+    {"256x128", 256, 128, 2, 4, 3, 1, 1.00f, 1.00f},
+    {"128x128w8s4", 128, 128, 2, 4, 4, 1, 0.90f, 0.90f},
+    {"128x64", 128, 64, 2, 2, 2, 3, 0.75f, 0.75f},
+    {"256x32", 256, 32, 4, 1, 2, 2, 0.70f, 0.70f},   // for at most 32 columns
+};
+constexpr Tile kTile64x256 = {"64x256", 64, 256, 2, 4, 3, 1, 0.90f, 0.90f};   // 8 waves of 32 x 64, 120 KB
+
+template <int MODE>
+int go3(const Tile &t, const Args &a, dim3 grid, hipStream_t st) {
+    if constexpr (MODE == kWgrad) {
+        if (t.bm == 64) return go<MODE, 64, 256, 2, 4, 3, 1, false, 1, true, true>(a, grid, st);
+        if (t.bm == 128 && t.stages == 2) return go<MODE, 128, 128, 2, 4, 2, 2, false, 1, true, true>(a, grid, st);
+    } else {
+        if (t.bn == 64) return go<MODE, 128, 64, 2, 2, 2, 3, false, 1, true, true>(a, grid, st);
+        if (t.bn == 32) return go<MODE, 256, 32, 4, 1, 2, 2, false, 1, true, true>(a, grid, st);
+    }
+    if (t.bm == 256 && t.bn == 128) return go<MODE, 256, 128, 2, 4, 3, 1, false, 1, true, true>(a, grid, st);
+    if (t.bm == 128 && t.bn == 128 && t.stages == 4) return go<MODE, 128, 128, 2, 4, 4, 1, false, 1, true, true>(a, grid, st);
+    return (int)hipErrorInvalidValue;
+}
+
+struct Plan3 {
+    Tile t;
+    int splits, k_split;
+};
+
+Plan3 with_split(const Tile &t, int splits, long K) {
+    const long per = std::max<long>(BK, ((K + splits - 1) / splits + BK - 1) / BK * BK);
+    return {t, K > 0 ? (int)((K + per - 1) / per) : 1, (int)per};
+}
+
+// `room`: bytes for the partials of `out` elements (the folded form's workspace,
+// so that no call needs more than it did)
+Plan3 plan3(long M, long N, long K, int z, int64_t out, int64_t room) {
+    double best = 1e300;
+    Tile bt = kTiles3[1];
+    int bs = 1;
+    const int most = (int)std::max<int64_t>(1, std::min<int64_t>({16, K / (4 * BK), room / (part_stride(out) * 4 + 256)}));
+    for (const Tile &t : kTiles3)
+        for (int sp = 1; sp <= most; ++sp) {
+            if (t.bn == 32 && N > 32) break;
+            const double us = est_us(t, M, N, K, z, sp);
+            if (us < best * 0.999) {
+                best = us;
+                bt = t;
+                bs = sp;
+            }
+        }
+    return with_split(bt, bs, K);
+}
+
+// As the 2-D weight gradient (pick_conv_wgrad) where there are more than 64
+// filters; else 64-row tiles, split until every CU has a block (a 128-row tile
+// does twice the work).
+Plan3 plan3_wgrad(long M, long N, long K, int64_t room) {
+    const long fit = (long)(room / ((M * N + M) * 4));
+    if (M > 64) {
+        int splits = 1;
+        const Tile t = pick_conv_wgrad(M, N, K, (int)std::max<long>(1, std::min(fit, K / (8 * BK))), &splits, true);
+        return with_split(t, splits, K);
+    }
+    // (half a microsecond a step; a split's partials are written and read at
+    // about 3 TB/s)
+    const long tiles = (N + 255) / 256, most = std::max<long>(1, std::min<long>({kCUs / tiles, K / (8 * BK), fit}));
+    double best = 1e300;
+    int bs = 1;
+    for (int sp = 1; sp <= most; ++sp) {
+        const double us = 0.5 * ((double)K / sp / BK + 4) + (sp > 1 ? sp * M * N * 8.0 / 3.0e6 : 0.0);
+        if (us < best) {
+            best = us;
+            bs = sp;
+        }
+    }
+    return with_split(kTile64x256, bs, K);
+}
+
+// The 3-D convolution's own geometry: q.g with C channels.
+ConvGeom geom3(const Conv3dGeom &q) {
+    ConvGeom g = q.g;
+    g.C = q.C;
+    return g;
+}
+long x3_elems(const Conv3dGeom &q) { return (long)q.N * q.Din * q.g.H * q.g.W * q.C; }
+long y3_elems(const Conv3dGeom &q) { return (long)q.N * q.Do * q.g.P * q.g.Q * q.g.K; }
+long w3_elems(const Conv3dGeom &q) { return (long)q.g.K * q.T * q.g.R * q.g.S * q.C; }
+bool fits3(const Conv3dGeom &q) {
+    return operand_fits(x3_elems(q)) && operand_fits(y3_elems(q)) && operand_fits(w3_elems(q)) && q.N > 0 && q.Do > 0 &&
+           q.Din > 0 && q.g.P > 0 && q.g.Q > 0 && q.g.H > 0 && q.g.W > 0;
+}
+// the input gradient's images are all Din depths of every sample
+ConvGeom dgeom3(const Conv3dGeom &q) {
+    ConvGeom g = geom3(q);
+    g.N = q.N * q.Din;
+    return g;
+}
+
+Plan3 fwd_plan3(const Conv3dGeom &q, size_t room) {
+    return plan3((long)q.g.N * q.g.P * q.g.Q, q.g.K, (long)q.T * q.g.R * q.g.S * q.C, 1, y3_elems(q), (int64_t)room);
+}
+Plan3 dgrad_plan3(const Conv3dGeom &q, size_t room) {
+    const ConvGeom &g = q.g;
+    const long Hb = (g.H + g.sh - 1) / g.sh, Wb = (g.W + g.sw - 1) / g.sw;
+    const long Kb = (long)q.T * ((g.R + g.sh - 1) / g.sh) * ((g.S + g.sw - 1) / g.sw) * g.K;
+    return plan3((long)q.N * q.Din * Hb * Wb, q.C, Kb, g.sh * g.sw, x3_elems(q),
+                 (int64_t)room - (int64_t)al256((size_t)w3_elems(q) * 2));
+}
+Plan3 wgrad_plan3(const Conv3dGeom &q, size_t room) {
+    return plan3_wgrad(q.g.K, (long)q.T * q.g.R * q.g.S * q.C, (long)q.g.N * q.g.P * q.g.Q, (int64_t)room);
+}
+
+// Forward: whole reduction steps in one tap and at most 32 taps; the input
+// gradient too (of a stride phase), at unit depth step (the phases are those of
+// height and width); the weight gradient any channel counts of whole vectors.
+bool fwd3_ok(const Conv3dGeom &q) { return q.C % BK == 0 && q.g.K % 8 == 0 && q.T * q.g.R * q.g.S <= 32 && fits3(q); }
+bool dgrad3_ok(const Conv3dGeom &q) {
+    const ConvGeom &g = q.g;
+    return q.sd == 1 && g.K % BK == 0 && q.C % 8 == 0 &&
+           q.T * ((g.R + g.sh - 1) / g.sh) * ((g.S + g.sw - 1) / g.sw) <= 32 && fits3(q);
+}
+bool wgrad3_ok(const Conv3dGeom &q) { return q.C % 8 == 0 && q.g.K % 8 == 0 && fits3(q); }
+
+}  // namespace
+
+// v = conv(u) + bias; each returns -1 when it does not apply (`room`: bytes of ws)
+int conv3d_fwd(const Conv3dGeom &q, const void *u, const void *w, const void *bias, void *v, void *ws, size_t room,
+               hipStream_t st) {
+    if (!fwd3_ok(q) || !al16(u) || !al16(w) || !al16(v) ) return -1;
+    const ConvGeom g = geom3(q);
+    const Plan3 p = fwd_plan3(q, room);
+    if (p.splits > 1 && (!ws || !al16(ws))) return -1;
+    Args a{};
+    a.a = (const bf16 *)u; a.b = (const bf16 *)w; a.g = g;
+    a.M = g.N * g.P * g.Q; a.N = g.K; a.K = q.T * g.R * g.S * g.C;
+    a.T = q.T; a.m_depth = q.Do; a.a_depth = q.Din; a.d_step = q.sd; a.d_off = -q.pd;
+    a.ntm = (a.M + p.t.bm - 1) / p.t.bm; a.ntn = (a.N + p.t.bn - 1) / p.t.bn;
+    a.splits = p.splits; a.k_split = p.k_split;
+    a.a_bytes = bytes_of(x3_elems(q)); a.b_bytes = bytes_of(w3_elems(q));
+    const int64_t n = y3_elems(q);
+    if (p.splits > 1) {
+        a.part = static_cast<float *>(ws);
+        a.part_stride = part_stride(n);
+    } else {
+        a.c = (bf16 *)v;
+        a.bias = (const bf16 *)bias;
+    }
+    const int err = go3<kFwd>(p.t, a, dim3(a.ntm * a.ntn, 1, p.splits), st);
+    if (err || p.splits <= 1) return err;
+    return reduce_partials(a.part, p.splits, n, a.part_stride, (bf16 *)v, (const bf16 *)bias, a.N, st);
+}
+
+int conv3d_dgrad(const Conv3dGeom &q, const void *dv, const void *w, const void *bias, void *du, void *ws, size_t room,
+                 hipStream_t st) {
+    if (!dgrad3_ok(q) || !al16(dv) || !al16(w) || !al16(du) || !ws || !al16(ws)) return -1;
+    const ConvGeom g = dgeom3(q);
+    if (room < al256((size_t)w3_elems(q) * 2)) return -1;
+    const Plan3 p = dgrad_plan3(q, room);
+    bf16 *wt = static_cast<bf16 *>(ws);   // [C][T][R][S][K]
+    int err = transpose_krsc(w, wt, g.K, q.T * g.R * g.S, g.C, st);
+    if (err) return err;
+    Args a{};
+    a.a = (const bf16 *)dv; a.b = wt; a.g = g;
+    const int Hb = (g.H + g.sh - 1) / g.sh, Wb = (g.W + g.sw - 1) / g.sw;
+    a.M = g.N * Hb * Wb; a.N = g.C;
+    a.K = q.T * ((g.R + g.sh - 1) / g.sh) * ((g.S + g.sw - 1) / g.sw) * g.K;
+    a.T = q.T; a.m_depth = q.Din; a.a_depth = q.Do; a.d_step = 1; a.d_off = q.pd;
+    a.ntm = (a.M + p.t.bm - 1) / p.t.bm; a.ntn = (a.N + p.t.bn - 1) / p.t.bn;
+    a.splits = p.splits; a.k_split = p.k_split;
+    a.a_bytes = bytes_of(y3_elems(q)); a.b_bytes = bytes_of(w3_elems(q));
+    const int64_t n = x3_elems(q);
+    if (p.splits > 1) {
+        a.part = reinterpret_cast<float *>(static_cast<char *>(ws) + al256((size_t)w3_elems(q) * 2));
+        a.part_stride = part_stride(n);
+    } else {
+        a.c = (bf16 *)du;
+        a.bias = (const bf16 *)bias;
+    }
+    err = go3<kDgrad>(p.t, a, dim3(a.ntm * a.ntn, 1, g.sh * g.sw * p.splits), st);
+    if (err || p.splits <= 1) return err;
+    return reduce_partials(a.part, p.splits, n, a.part_stride, (bf16 *)du, (const bf16 *)bias, g.C, st);
+}
+
+int conv3d_wgrad(const Conv3dGeom &q, const void *dv, const void *u, void *dw, void *db, void *ws, size_t room,
+                 hipStream_t st) {
+    if (!wgrad3_ok(q) || !al16(dv) || !al16(u) || !al16(dw) || !ws || !al16(ws)) return -1;
+    const ConvGeom g = geom3(q);
+    const Plan3 p = wgrad_plan3(q, room);
+    if (room < ((p.splits > 1 ? (size_t)p.splits * w3_elems(q) : 0) + (db ? (size_t)p.splits * q.g.K : 0)) * sizeof(float)) return -1;
+    Args a{};
+    a.a = (const bf16 *)dv; a.b = (const bf16 *)u; a.g = g;
+    a.M = g.K; a.N = q.T * g.R * g.S * g.C; a.K = g.N * g.P * g.Q;
+    a.T = q.T; a.m_depth = q.Do; a.a_depth = q.Din; a.d_step = q.sd; a.d_off = -q.pd;
+    a.ntm = (a.M + p.t.bm - 1) / p.t.bm; a.ntn = (a.N + p.t.bn - 1) / p.t.bn;
+    a.splits = p.splits; a.k_split = p.k_split;
+    a.a_bytes = bytes_of(y3_elems(q)); a.b_bytes = bytes_of(x3_elems(q));
+    float *wsf = static_cast<float *>(ws);
+    size_t used = 0;
+    if (p.splits > 1) {
+        a.part = wsf;
+        a.part_stride = (int64_t)a.M * a.N;
+        used = (size_t)p.splits * a.M * a.N;
+    } else {
+        a.c = (bf16 *)dw;
+    }
+    a.dbpart = db ? wsf + used : nullptr;
+    int err = go3<kWgrad>(p.t, a, dim3(a.ntm * a.ntn, 1, p.splits), st);
+    if (!err && (p.splits > 1 || db)) {
+        const int64_t n = p.splits > 1 ? (int64_t)a.M * a.N : 0;
+        const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>((n / 4 + 255) / 256, 2048));
+        hipLaunchKernelGGL(reduce_kernel, dim3(blocks), dim3(256), 0, st, (const float *)a.part, p.splits, n, n, (bf16 *)dw,
+                           (const float *)a.dbpart, db ? a.M : 0, (bf16 *)db, (const bf16 *)nullptr, 1);
         err = (int)hipGetLastError();
     }
     return err;
