@@ -19,6 +19,10 @@ struct ConvGeom {
     int K, R, S;      // filters
     int P, Q;         // output extent
     int sh, sw, ph, pw;
+    // the launchers take no more workspace than the passes cannot do without (fp32
+    // forwards and input gradients: none, they run unsplit): what the runtime falls
+    // back to where the workspace cannot be had
+    int lean = 0;
 };
 
 // y = W * x + b (b may be null).  May use conv_fwd_workspace() bytes of
@@ -132,7 +136,10 @@ int launch_copy4(int dtype, const void *src, const int64_t ext[4], const int64_t
                  const int64_t dstride[4], void *stream);
 
 // Per-stream transient workspace (workspace.hip).  Returns null and sets
-// *err on failure.
+// *err on failure: 1 unavailable, 2 another HIP error.  With *err negative on
+// entry the caller can do with less: where the buffer would have to grow while
+// the stream is being captured, nothing is allocated and *err is kWsCapture.
+constexpr int kWsCapture = 3;
 void *workspace_get(void *stream, size_t bytes, int *err);
 // Test hook: make the next `n` workspace growths fail.
 void workspace_fail_next(int n);

@@ -642,7 +642,7 @@ SplitPlan wgrad_split(int dtype, const ConvGeom &g) {
 }  // namespace
 
 size_t conv_fwd_workspace(int dtype, const ConvGeom &g) {
-    return dtype == kBF16 ? g2::fwd_workspace(g) : f32g::fwd_workspace(g);
+    return dtype == kBF16 ? g2::fwd_workspace(g) : g.lean ? 0 : f32g::fwd_workspace(g);
 }
 
 int launch_conv_fwd(int dtype, const ConvGeom &g, const void *x, const void *w, const void *bias,
@@ -651,7 +651,7 @@ int launch_conv_fwd(int dtype, const ConvGeom &g, const void *x, const void *w, 
         const int r = g2::conv_fwd(g, x, w, bias, y, ws, (hipStream_t)stream);
         if (r >= 0) return r;
     } else {
-        const int r = f32g::conv_fwd(g, x, w, bias, y, ws, (hipStream_t)stream);
+        const int r = f32g::conv_fwd(g, x, w, bias, y, g.lean ? nullptr : ws, (hipStream_t)stream);
         if (r >= 0) return r;
     }
     IgemmParams prm{};
@@ -671,7 +671,7 @@ int launch_conv_fwd(int dtype, const ConvGeom &g, const void *x, const void *w, 
 }
 
 size_t conv_dgrad_workspace(int dtype, const ConvGeom &g, bool with_db) {
-    return dtype == kBF16 ? g2::dgrad_workspace(g, with_db) : f32g::dgrad_workspace(g);
+    return dtype == kBF16 ? g2::dgrad_workspace(g, with_db) : g.lean ? 0 : f32g::dgrad_workspace(g);
 }
 
 int launch_conv_dgrad(int dtype, const ConvGeom &g, const void *dy, const void *w, const void *bias,
@@ -681,7 +681,7 @@ int launch_conv_dgrad(int dtype, const ConvGeom &g, const void *dy, const void *
         const int r = g2::conv_dgrad(g, dy, w, bias, dx, ws, (hipStream_t)stream, db, db_done);
         if (r >= 0) return r;
     } else {
-        const int r = f32g::conv_dgrad(g, dy, w, bias, dx, ws, (hipStream_t)stream);
+        const int r = f32g::conv_dgrad(g, dy, w, bias, dx, g.lean ? nullptr : ws, (hipStream_t)stream);
         if (r >= 0) return r;
     }
     IgemmParams prm{};

@@ -612,6 +612,24 @@ uint32_t kernel_bits(int32_t kind, uint32_t mask) {
     return k;
 }
 
+size_t forward_workspace(const Plan &pl) {
+    switch (pl.kind) {
+    case MS_CONV2D:
+    case MS_LINEAR: return ms::conv_fwd_workspace(pl.dtype, pl.g);
+    case MS_CONV_TRANSPOSE2D: return ms::conv_dgrad_workspace(pl.dtype, pl.g);
+    case MS_CONV3D: return ms::conv3d_fwd_workspace(pl.dtype, pl.q);
+    case MS_CONV_TRANSPOSE3D: return ms::conv3d_dgrad_workspace(pl.dtype, pl.q);
+    default: return 0;
+    }
+}
+
+// The same layer on the least workspace (ConvGeom::lean).
+Plan lean_plan(const Plan &pl) {
+    Plan l = pl;
+    l.g.lean = l.q.g.lean = 1;
+    return l;
+}
+
 size_t backward_workspace(const Plan &pl, uint32_t kernels) {
     size_t ws = 0;
     if (pl.kind == MS_CONV2D || pl.kind == MS_LINEAR) {
@@ -808,19 +826,26 @@ ms_status ms_layer_forward(const ms_layer *layer, const ms_tensor *x, const ms_t
     const size_t ox = stg ? sg.add(x) : kNoStage;
     const size_t ow = stg && W && W->ndim >= 2 ? sg.add(W) : kNoStage;
     const size_t oy = stg ? sg.add(y) : kNoStage;
-    size_t fb = 0;
-    if (pl.kind == MS_CONV2D || pl.kind == MS_LINEAR || pl.kind == MS_CONV_TRANSPOSE2D || pl.kind == MS_CONV3D ||
-        pl.kind == MS_CONV_TRANSPOSE3D)
-        fb = pl.kind == MS_CONV_TRANSPOSE2D    ? ms::conv_dgrad_workspace(pl.dtype, pl.g)
-             : pl.kind == MS_CONV3D            ? ms::conv3d_fwd_workspace(pl.dtype, pl.q)
-             : pl.kind == MS_CONV_TRANSPOSE3D ? ms::conv3d_dgrad_workspace(pl.dtype, pl.q)
-                                               : ms::conv_fwd_workspace(pl.dtype, pl.g);
+    size_t fb = forward_workspace(pl);
+    const Plan *run = &pl;
+    Plan lean;
     char *base = nullptr;
     if (sg.bytes + fb) {
-        int werr = 0;
+        int werr = -1;
         base = static_cast<char *>(ms::workspace_get(stream, sg.bytes + fb, &werr));
-        if (!base) return werr == 1 ? fail(MS_E_NOMEM, "workspace of %zu bytes unavailable", sg.bytes + fb)
-                                    : hip_fail(ms::device_last_error(), "workspace");
+        if (werr == 1 || werr == ms::kWsCapture) {
+            // the layer on the least it can do with
+            lean = lean_plan(pl);
+            run = &lean;
+            const size_t less = forward_workspace(lean);
+            if (less < fb || werr == ms::kWsCapture) {
+                fb = less;
+                werr = 0;
+                if (sg.bytes + fb) base = static_cast<char *>(ms::workspace_get(stream, sg.bytes + fb, &werr));
+            }
+        }
+        if (werr) return werr == 1 ? fail(MS_E_NOMEM, "workspace of %zu bytes unavailable", sg.bytes + fb)
+                                   : hip_fail(ms::device_last_error(), "workspace");
     }
     void *fws = fb ? base + sg.bytes : nullptr;
     ms_record *r = nullptr;
@@ -835,16 +860,16 @@ ms_status ms_layer_forward(const ms_layer *layer, const ms_tensor *x, const ms_t
     if (!err) switch (pl.kind) {
     case MS_CONV2D:
     case MS_LINEAR:
-        err = ms::launch_conv_fwd(pl.dtype, pl.g, xk, wk, b ? b->data : nullptr, yk, fws, stream);
+        err = ms::launch_conv_fwd(pl.dtype, run->g, xk, wk, b ? b->data : nullptr, yk, fws, stream);
         break;
     case MS_CONV_TRANSPOSE2D:   // the input-gradient contraction of the convolution y -> x, plus b
-        err = ms::launch_conv_dgrad(pl.dtype, pl.g, xk, wk, b ? b->data : nullptr, yk, fws, stream);
+        err = ms::launch_conv_dgrad(pl.dtype, run->g, xk, wk, b ? b->data : nullptr, yk, fws, stream);
         break;
     case MS_CONV3D:
-        err = ms::launch_conv3d_fwd(pl.dtype, pl.q, x->data, W->data, b ? b->data : nullptr, y->data, fws, stream);
+        err = ms::launch_conv3d_fwd(pl.dtype, run->q, x->data, W->data, b ? b->data : nullptr, y->data, fws, stream);
         break;
     case MS_CONV_TRANSPOSE3D:
-        err = ms::launch_conv3d_dgrad(pl.dtype, pl.q, x->data, W->data, b ? b->data : nullptr, y->data, fws, stream);
+        err = ms::launch_conv3d_dgrad(pl.dtype, run->q, x->data, W->data, b ? b->data : nullptr, y->data, fws, stream);
         break;
     case MS_BN_EVAL:
         if (pl.bn_nchw)
@@ -909,57 +934,64 @@ ms_status backward_impl(ms_record *r, const ms_tensor *grad_y, const ms_tensor *
     if (r->magic != kMagic) return fail(MS_E_ARG, "not a live record");
     if (r->consumed) return fail(MS_E_CONSUMED, "backward already ran on this record");
     const uint32_t mask = r->acct.mask;
-    const Plan &pl = r->plan;
+    const Plan &full = r->plan;
     if ((grad_x != nullptr) != bool(mask & MS_RG_INPUT))
         return fail(MS_E_MASK, "grad_x must be given exactly when the INPUT bit is set");
     if ((grad_W != nullptr) != bool(mask & MS_RG_WEIGHT))
         return fail(MS_E_MASK, "grad_W must be given exactly when the WEIGHT bit is set");
     if ((grad_b != nullptr) != bool(mask & MS_RG_BIAS))
         return fail(MS_E_MASK, "grad_b must be given exactly when the BIAS bit is set");
-    ms_status st = check_grad(grad_y, &r->y, "grad_y", pl.kind, false);
+    ms_status st = check_grad(grad_y, &r->y, "grad_y", full.kind, false);
     if (st) return st;
-    if (grad_x && (st = check_grad(grad_x, &r->x, "grad_x", pl.kind, true))) return st;
-    if (grad_W && (st = check_grad(grad_W, &r->W, "grad_W", pl.kind, true))) return st;
-    if (grad_b && (st = check_grad(grad_b, &r->b, "grad_b", pl.kind, true))) return st;
+    if (grad_x && (st = check_grad(grad_x, &r->x, "grad_x", full.kind, true))) return st;
+    if (grad_W && (st = check_grad(grad_W, &r->W, "grad_W", full.kind, true))) return st;
+    if (grad_b && (st = check_grad(grad_b, &r->b, "grad_b", full.kind, true))) return st;
 
     const uint32_t kernels = r->acct.kernels;
     // stand-ins of tensors in other layouts, then the kernels' workspace
     Stager sg;
     // BN-eval wanting dx alone on plain NCHW tensors: the in-place sweep
-    const bool bn_native = pl.kind == MS_BN_EVAL && kernels == MS_K_DGRAD && grad_y->ndim == 4 && !canonical(grad_y) &&
+    const bool bn_native = full.kind == MS_BN_EVAL && kernels == MS_K_DGRAD && grad_y->ndim == 4 && !canonical(grad_y) &&
                            is_nchw(grad_y) && !canonical(grad_x) && is_nchw(grad_x);
-    const bool stg = stageable(pl.kind) && !bn_native;
-    const bool x_read = (kernels & MS_K_WGRAD) && pl.kind != MS_AVGPOOL;   // weight gradient (BN: dgamma)
-    const bool w_read = (kernels & MS_K_DGRAD) && pl.kind != MS_BN_EVAL && pl.kind != MS_AVGPOOL;
+    const bool stg = stageable(full.kind) && !bn_native;
+    const bool x_read = (kernels & MS_K_WGRAD) && full.kind != MS_AVGPOOL;   // weight gradient (BN: dgamma)
+    const bool w_read = (kernels & MS_K_DGRAD) && full.kind != MS_BN_EVAL && full.kind != MS_AVGPOOL;
     const size_t ody = stg ? sg.add(grad_y) : kNoStage;
     const size_t ox = stg && x_read ? sg.add(&r->x) : kNoStage;
     const size_t ow = stg && w_read ? sg.add(&r->W) : kNoStage;
     const size_t ogx = stg && grad_x ? sg.add(grad_x) : kNoStage;
     const size_t ogw = stg && grad_W && grad_W->ndim >= 2 ? sg.add(grad_W) : kNoStage;
-    size_t kb = backward_workspace(pl, kernels);
-    // an fp32 input gradient takes workspace only to split its reduction and
-    // runs unsplit without: so it does when the fixed scratch cannot hold both
-    // the stand-ins and its partials
-    bool dgrad_ws = true;
-    if (fixed_scratch && pl.dtype == MS_F32 && (kernels & MS_K_DGRAD) && sg.bytes + kb > ms::kScratchBytes &&
-        (pl.kind == MS_CONV2D || pl.kind == MS_LINEAR || pl.kind == MS_CONV_TRANSPOSE2D)) {
-        kb = backward_workspace(pl, kernels & ~(uint32_t)MS_K_DGRAD);
-        dgrad_ws = false;
-    }
-    const size_t ws_bytes = sg.bytes + kb;
+    size_t kb = backward_workspace(full, kernels);
+    Plan lean;
+    const Plan *run = &full;
+    // the layer on the least it can do with, where its workspace cannot be had:
+    // whether that is less
+    auto go_lean = [&]() {
+        lean = lean_plan(full);
+        run = &lean;
+        const size_t was = kb;
+        kb = backward_workspace(lean, kernels);
+        return kb < was;
+    };
     char *base = nullptr;
-    if (ws_bytes && fixed_scratch) {
-        int werr = 0;
-        base = static_cast<char *>(ms::scratch_get(ws_bytes, &werr));
-        if (!base) return werr == 1 ? fail(MS_E_UNSUPPORTED, "backward needs %zu bytes of scratch; the fixed scratch "
-                                                             "holds %zu", ws_bytes, ms::kScratchBytes)
-                                    : hip_fail(ms::device_last_error(), "scratch lookup");
-    } else if (ws_bytes) {
-        int werr = 0;
-        base = static_cast<char *>(ms::workspace_get(stream, ws_bytes, &werr));
-        if (!base) return werr == 1 ? fail(MS_E_NOMEM, "workspace of %zu bytes unavailable", ws_bytes)
-                                    : hip_fail(ms::device_last_error(), "workspace");
+    int werr = 0;
+    if (fixed_scratch) {
+        if (sg.bytes + kb > ms::kScratchBytes) go_lean();
+        if (sg.bytes + kb) base = static_cast<char *>(ms::scratch_get(sg.bytes + kb, &werr));
+        if (werr) return werr == 1 ? fail(MS_E_UNSUPPORTED, "backward needs %zu bytes of scratch; the fixed scratch "
+                                                            "holds %zu", sg.bytes + kb, ms::kScratchBytes)
+                                   : hip_fail(ms::device_last_error(), "scratch lookup");
+    } else if (sg.bytes + kb) {
+        werr = -1;
+        base = static_cast<char *>(ms::workspace_get(stream, sg.bytes + kb, &werr));
+        if ((werr == 1 || werr == ms::kWsCapture) && (go_lean() || werr == ms::kWsCapture)) {
+            werr = 0;
+            if (sg.bytes + kb) base = static_cast<char *>(ms::workspace_get(stream, sg.bytes + kb, &werr));
+        }
+        if (werr) return werr == 1 ? fail(MS_E_NOMEM, "workspace of %zu bytes unavailable", sg.bytes + kb)
+                                   : hip_fail(ms::device_last_error(), "workspace");
     }
+    const Plan &pl = *run;
     void *ws = kb ? base + sg.bytes : nullptr;
     int err = stage_in(grad_y, base, ody, stream);
     if (!err) err = stage_in(&r->x, base, ox, stream);
@@ -977,7 +1009,7 @@ ms_status backward_impl(ms_record *r, const ms_tensor *grad_y, const ms_tensor *
         bool db_done = false;
         void *db_dgrad = (kernels & MS_K_BGRAD) && !(kernels & MS_K_WGRAD) ? grad_b->data : nullptr;
         if (!err && (kernels & MS_K_DGRAD))
-            err = ms::launch_conv_dgrad(pl.dtype, pl.g, dy, wk, nullptr, gx, dgrad_ws ? ws : nullptr, stream, db_dgrad,
+            err = ms::launch_conv_dgrad(pl.dtype, pl.g, dy, wk, nullptr, gx, ws, stream, db_dgrad,
                                         &db_done);
         if (!err && (kernels & MS_K_WGRAD))
             err = ms::launch_conv_wgrad(pl.dtype, pl.g, dy, xk, gw, (kernels & MS_K_BGRAD) ? grad_b->data : nullptr, ws,
@@ -993,7 +1025,7 @@ ms_status backward_impl(ms_record *r, const ms_tensor *grad_y, const ms_tensor *
         // weight gradient with x as its output gradient and grad_y as its input
         bool db_unused = false;
         if (kernels & MS_K_DGRAD)
-            err = ms::launch_conv_fwd(pl.dtype, pl.g, dy, wk, nullptr, gx, dgrad_ws ? ws : nullptr, stream);
+            err = ms::launch_conv_fwd(pl.dtype, pl.g, dy, wk, nullptr, gx, ws, stream);
         if (!err && (kernels & MS_K_WGRAD))
             err = ms::launch_conv_wgrad(pl.dtype, pl.g, xk, dy, gw, nullptr, ws, stream, &db_unused);
         if (!err && (kernels & MS_K_BGRAD))

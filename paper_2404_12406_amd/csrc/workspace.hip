@@ -34,6 +34,7 @@ void workspace_fail_next(int n) { g_fail_next.store(n); }
 
 // err: 0 ok, 1 allocation failed, 2 other HIP error
 void *workspace_get(void *stream, size_t bytes, int *err) {
+    const bool optional = *err < 0;
     *err = 0;
     if (bytes == 0) return nullptr;
     int dev = 0;
@@ -44,6 +45,18 @@ void *workspace_get(void *stream, size_t bytes, int *err) {
     std::lock_guard<std::mutex> lk(g_mu);
     Buf &b = g_bufs[{dev, stream}];
     if (b.n >= bytes) return b.p;
+    if (optional) {
+        // allocating would end the capture
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing((hipStream_t)stream, &cs) != hipSuccess) {
+            (void)hipGetLastError();
+            cs = hipStreamCaptureStatusActive;
+        }
+        if (cs != hipStreamCaptureStatusNone) {
+            *err = kWsCapture;
+            return nullptr;
+        }
+    }
     if (g_fail_next.load() > 0) {
         g_fail_next.fetch_sub(1);
         *err = 1;

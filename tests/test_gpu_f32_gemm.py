@@ -128,3 +128,35 @@ def test_f32_few_channel_weight_gradient_keeps_infinities_apart():
         gw = host(gw)
         assert not np.isnan(gw).any() and np.isfinite(np.delete(gw, 5, 1)).all()
         assert np.isinf(gw[:, 5, 1, 1]).all()
+
+
+def test_f32_passes_captured_without_workspace():
+    """A capture on a stream that holds no workspace: the passes that would split
+    their reduction for it run unsplit instead of allocating."""
+    xs, ws = (1, 128, 4, 4), (256, 128, 3, 3)
+    x, w = synth.normal(xs, 9700, dtype="f32"), synth.kaiming_uniform(ws, 9701, 1152, dtype="f32")
+    gy = synth.normal((1, 256, 4, 4), 9702, dtype="f32")
+    X, W, G = (dev(t, "f32") for t in (x, w, gy))
+
+    def passes():
+        y, rec = ms.layer_forward(ms.Conv2d(1, 1), X, W, None, 1)
+        return y, ms.layer_backward(rec, G)[0]
+
+    def right(y, dx):
+        torch.cuda.synchronize()
+        ax, aw, ag = np.abs(x), np.abs(w), np.abs(gy)
+        _within("y", host(y), oracle.conv2d_forward(x, w, None, (1, 1), (1, 1)),
+                oracle.conv2d_forward(ax, aw, None, (1, 1), (1, 1)), 1152)
+        _within("dx", host(dx), oracle.conv2d_input_grad(gy, w, xs, (1, 1), (1, 1)),
+                oracle.conv2d_input_grad(ag, aw, xs, (1, 1), (1, 1)), 2304)
+
+    right(*passes())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        got = passes()
+    for _ in range(3):
+        for t in got:
+            t.fill_(float("nan"))
+        graph.replay()
+        right(*got)
+        right(*passes())
