@@ -760,22 +760,69 @@ int transpose_krsc(const void *w, bf16 *wt, int K, int RS, int C, hipStream_t st
     return (int)hipGetLastError();
 }
 
-// Channel counts that are not a multiple of 8 (the 3-channel stem): the fast
-// path runs on copies whose channels are padded with zeros to C8 =
-// roundup(C, 8).  dst[row][c] = c < C ? src[row][c] : 0, one 16-byte row
-// vector per thread.
-__global__ __launch_bounds__(256) void pad_channels_kernel(const bf16 *__restrict__ src, int64_t rows, int C, int C8,
-                                                           bf16 *__restrict__ dst) {
-    const int nv = C8 / 8;
-    const int64_t total = rows * nv;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t row = i / nv;
-        const int c0 = (int)(i - row * nv) * 8;
-        Vec16<bf16> v;
+// The same for channel counts that are not multiples of 8: Wt[c][rs][k] =
+// W[k][rs][c], zero for k >= K or c >= C, of rows c < Cr and ldk k's each.  32 x
+// 32 tiles through LDS (small: a filter of a few ten thousand elements has to
+// reach many CUs), adjacent elements by adjacent lanes both ways.
+// Grid (ceil(Cr/32), ceil(ldk/32), R*S).
+__global__ __launch_bounds__(256) void transpose_ragged_kernel(const bf16 *__restrict__ W, bf16 *__restrict__ Wt, int K,
+                                                               int RS, int C, int ldk, int Cr) {
+    __shared__ bf16 tile[32][34];
+    const int c0 = blockIdx.x * 32, k0 = blockIdx.y * 32, rs = blockIdx.z;
+    const int lane = threadIdx.x & 31, row = threadIdx.x >> 5;
+    bf16 v[4];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v.e[e] = c0 + e < C ? src[row * C + c0 + e] : (bf16)0.f;
-        store16(dst + row * C8 + c0, v);
+    for (int i = 0; i < 4; ++i)   // (the last element where there is none: no branch around the load)
+        v[i] = W[((size_t)min(k0 + i * 8 + row, K - 1) * RS + rs) * C + min(c0 + lane, C - 1)];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        tile[i * 8 + row][lane] = k0 + i * 8 + row < K && c0 + lane < C ? v[i] : (bf16)0.f;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int c = c0 + i * 8 + row, k = k0 + lane;
+        if (c < Cr && k < ldk) Wt[((size_t)c * RS + rs) * ldk + k] = tile[lane][i * 8 + row];
+    }
+}
+
+// Channel counts that are not a multiple of 8: the contractions read copies
+// whose pixels are padded with zeros to C8 = roundup(C, 8) channels.
+// dst[row][c] = c < C ? src[row][c] : 0, one 16-byte vector of a row per thread,
+// read in pieces of V channels (V divides C; a piece is aligned like its row).
+struct PadSrc {
+    const bf16 *src;
+    bf16 *dst;
+    int64_t rows, total;   // total = rows * C8 / 8 vectors
+    int C, C8;
+};
+template <int V>
+__device__ __forceinline__ void pad_vector(const PadSrc &p, int64_t i) {
+    struct alignas(2 * V) Piece {
+        bf16 e[V];
+    };
+    const int nv = p.C8 / 8;
+    const int64_t row = p.total <= 0x7fffffff ? (int64_t)((uint32_t)i / (uint32_t)nv) : i / nv;
+    const int c0 = (int)(i - row * nv) * 8;
+    const bf16 *s = p.src + row * p.C + c0;
+    Vec16<bf16> v;
+#pragma unroll
+    for (int e = 0; e < 8; e += V) {
+        Piece q;
+#pragma unroll
+        for (int u = 0; u < V; ++u) q.e[u] = (bf16)0.f;
+        if (c0 + e < p.C) q = *reinterpret_cast<const Piece *>(s + e);
+#pragma unroll
+        for (int u = 0; u < V; ++u) v.e[e + u] = q.e[u];
+    }
+    store16(p.dst + row * p.C8 + c0, v);
+}
+// Both operands of a contraction in one launch (b.total may be 0).
+template <int V>
+__global__ __launch_bounds__(256) void pad_channels_kernel(PadSrc a, PadSrc b) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.total + b.total;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        if (i < a.total) pad_vector<V>(a, i);
+        else pad_vector<V>(b, i - a.total);
     }
 }
 
@@ -1012,18 +1059,36 @@ __global__ __launch_bounds__(256) void crop_channels_kernel(const bf16 *__restri
 
 // Sum split-K partials (and fused bias-gradient partials) to bf16; with a
 // bias, out[i] also gets bias[i % ncol] (added in fp32 before the rounding).
+// CROP: rows of C8 (a multiple of 4) partials keep their first C elements.
+template <bool CROP>
 __global__ __launch_bounds__(256) void reduce_kernel(const float *__restrict__ part, int splits, int64_t n,
                                                      int64_t pstride, bf16 *__restrict__ out, const float *__restrict__ dbpart,
                                                      int M, bf16 *__restrict__ db, const bf16 *__restrict__ bias,
-                                                     int ncol) {
+                                                     int ncol, int C8 = 4, int C = 4) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t nv = n / 4;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nv; i += stride) {
         floatx4 s = *reinterpret_cast<const floatx4 *>(part + 4 * i);
-        for (int z = 1; z < splits; ++z) s += *reinterpret_cast<const floatx4 *>(part + (int64_t)z * pstride + 4 * i);
+        int z = 1;
+        for (; z + 6 <= splits; z += 6) {   // six loads in flight, summed in their order
+            floatx4 t[6];
+#pragma unroll
+            for (int u = 0; u < 6; ++u) t[u] = *reinterpret_cast<const floatx4 *>(part + (int64_t)(z + u) * pstride + 4 * i);
+#pragma unroll
+            for (int u = 0; u < 6; ++u) s += t[u];
+        }
+        for (; z < splits; ++z) s += *reinterpret_cast<const floatx4 *>(part + (int64_t)z * pstride + 4 * i);
         if (bias) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) s[e] += (float)bias[(4 * i + e) % ncol];
+        }
+        if constexpr (CROP) {
+            const int64_t row = 4 * i / C8;
+            const int c = (int)(4 * i - row * C8);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (c + e < C) out[row * C + c + e] = (bf16)s[e];
+            continue;
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) out[4 * i + e] = (bf16)s[e];
@@ -1389,12 +1454,33 @@ uint32_t bytes_of(long elems) { return (uint32_t)(elems * 2); }
 int pad8(int c) { return (c + 7) / 8 * 8; }
 size_t al256(size_t n) { return (n + 255) / 256 * 256; }
 
-int pad_channels(const void *src, int64_t rows, int C, void *dst, hipStream_t st) {
-    const int C8 = pad8(C);
-    const int64_t total = rows * (C8 / 8);
+PadSrc pad_src(const void *src, int64_t rows, int C, int C8, void *dst) {
+    return {static_cast<const bf16 *>(src), static_cast<bf16 *>(dst), rows, rows * (C8 / 8), C, C8};
+}
+
+int pad_channels(const PadSrc &a, const PadSrc &b, hipStream_t st) {
+    const int64_t total = a.total + b.total;
     if (total == 0) return 0;
-    const int blocks = (int)std::min<int64_t>((total + 255) / 256, 8192);
-    hipLaunchKernelGGL(pad_channels_kernel, dim3(blocks), dim3(256), 0, st, (const bf16 *)src, rows, C, C8, (bf16 *)dst);
+    const dim3 grid((unsigned)std::min<int64_t>((total + 255) / 256, 8192));
+    auto splits = [&](int v) {   // whether every row splits into pieces of v channels, aligned
+        auto one = [&](const PadSrc &p) {
+            return p.total == 0 || (p.C % v == 0 && reinterpret_cast<uintptr_t>(p.src) % (2 * v) == 0);
+        };
+        return one(a) && one(b);
+    };
+    if (splits(4)) hipLaunchKernelGGL(pad_channels_kernel<4>, grid, dim3(256), 0, st, a, b);
+    else if (splits(2)) hipLaunchKernelGGL(pad_channels_kernel<2>, grid, dim3(256), 0, st, a, b);
+    else hipLaunchKernelGGL(pad_channels_kernel<1>, grid, dim3(256), 0, st, a, b);
+    return (int)hipGetLastError();
+}
+int pad_channels(const PadSrc &a, hipStream_t st) { return pad_channels(a, PadSrc{}, st); }
+
+// Wt[Cr][RS][ldk] from W[K][RS][C] (ldk and Cr: K and C or more, the rest zeros)
+int transpose_filter(const void *w, bf16 *wt, int K, int RS, int C, int ldk, int Cr, hipStream_t st) {
+    if (K == ldk && C == Cr && C % 8 == 0 && K % 8 == 0 && al16(w)) return transpose_krsc(w, wt, K, RS, C, st);
+    if (Cr == 0 || ldk == 0 || RS == 0) return 0;
+    hipLaunchKernelGGL(transpose_ragged_kernel, dim3((Cr + 31) / 32, (ldk + 31) / 32, RS), dim3(256), 0, st,
+                       (const bf16 *)w, wt, K, RS, C, ldk, Cr);
     return (int)hipGetLastError();
 }
 
@@ -1530,6 +1616,20 @@ ConvGeom padded(const ConvGeom &g) {
     return g8;
 }
 
+// Channels padded for a reduction over them and several taps: whole BK-deep
+// steps in one tap (tap-step loads) where that adds at most a quarter (32 x 28 x
+// 28, 96 -> 128 channels: the step's divisions cost 38%, the gradient through 96
+// 23.8 us, through 128 17.3).  Lean workspaces and one tap: multiples of 8.
+int pad_steps(const ConvGeom &g, int c) {
+    const int c8 = pad8(c), c64 = (c + BK - 1) / BK * BK;
+    return !g.lean && g.R * g.S > 1 && 4 * c64 <= 5 * c8 ? c64 : c8;
+}
+ConvGeom padded_fwd(const ConvGeom &g) {
+    ConvGeom q = g;
+    q.C = pad_steps(g, g.C);
+    return q;
+}
+
 struct WgradPlan {
     Tile t;
     int splits, k_split;
@@ -1619,7 +1719,7 @@ WgradPlan wgrad_plan(const ConvGeom &g) {
 int reduce_partials(const float *part, int splits, int64_t n, int64_t pstride, bf16 *out, const bf16 *bias, int ncol,
                     hipStream_t st) {
     const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>((n / 4 + 255) / 256, 4096));
-    hipLaunchKernelGGL(reduce_kernel, dim3(blocks), dim3(256), 0, st, part, splits, n, pstride, out,
+    hipLaunchKernelGGL(reduce_kernel<false>, dim3(blocks), dim3(256), 0, st, part, splits, n, pstride, out,
                        (const float *)nullptr, 0, (bf16 *)nullptr, bias, ncol);
     return (int)hipGetLastError();
 }
@@ -1805,9 +1905,8 @@ size_t fwd_workspace(const ConvGeom &g) {
     if (g.C % 8 == 0) return fwd_split_bytes(g);
     if (halo_block_fwd_applies(g)) return block_x_bytes(g) + block_w_bytes(g);
     if (pair_applies(g)) return pair_x_bytes(g) + pair_w_bytes(g) + fwd_split_bytes(paired(g));
-    const int C8 = pad8(g.C);
-    return al256((size_t)g.N * g.H * g.W * C8 * 2) + al256((size_t)g.K * g.R * g.S * C8 * 2) +
-           fwd_split_bytes(padded(g));
+    const ConvGeom g8 = padded_fwd(g);
+    return al256((size_t)g.N * g.H * g.W * g8.C * 2) + al256((size_t)g.K * g.R * g.S * g8.C * 2) + fwd_split_bytes(g8);
 }
 
 int conv_fwd(const ConvGeom &g, const void *x, const void *w, const void *bias, void *y, void *ws, hipStream_t st) {
@@ -1835,12 +1934,12 @@ int conv_fwd(const ConvGeom &g, const void *x, const void *w, const void *bias, 
     }
     if (g.C % 8 != 0) {
         if (!ws || !al16(ws) || !al16(y)) return -1;
-        const ConvGeom g8 = padded(g);
+        const ConvGeom g8 = padded_fwd(g);
         char *xp = static_cast<char *>(ws);
         char *wp = xp + al256((size_t)g.N * g.H * g.W * g8.C * 2);
         char *ws2 = wp + al256((size_t)g.K * g.R * g.S * g8.C * 2);
-        int err = pad_channels(x, (int64_t)g.N * g.H * g.W, g.C, xp, st);
-        if (!err) err = pad_channels(w, (int64_t)g.K * g.R * g.S, g.C, wp, st);
+        const int err = pad_channels(pad_src(x, (int64_t)g.N * g.H * g.W, g.C, g8.C, xp),
+                                     pad_src(w, (int64_t)g.K * g.R * g.S, g.C, g8.C, wp), st);
         if (err) return err;
         return conv_fwd(g8, xp, wp, bias, y, ws2, st);
     }
@@ -1907,7 +2006,7 @@ struct DgradChoice {
     GemmPlan p;
 };
 
-DgradChoice dgrad_choice(const ConvGeom &g) {
+DgradChoice dgrad_choice(const ConvGeom &g, bool ragged = false) {
     // GEMM bounds over the stride phases: ceil(H/sh) x ceil(W/sw) rows per
     // image, ceil(R/sh) x ceil(S/sw) taps
     const long Hb = (g.H + g.sh - 1) / g.sh, Wb = (g.W + g.sw - 1) / g.sw;
@@ -1922,11 +2021,11 @@ DgradChoice dgrad_choice(const ConvGeom &g) {
     // the narrow and 192-wide tiles read W through the transposed copy only
     const bool kc_forced = forced >= 0 && kc_only(kTiles[forced]);
     if (e && *e && !kc_forced) {
-        const bool direct = e[0] == 'd';
+        const bool direct = e[0] == 'd' && !ragged;
         return {direct, plan_gemm(M, g.C, Kb, z, direct ? 1 : 16, direct || unit, kg, direct ? kAuto : set)};
     }
     const GemmPlan pt = plan_gemm(M, g.C, Kb, z, 16, unit, kg, set);
-    if (!unit) return {false, pt};
+    if (!unit || ragged) return {false, pt};
     if (narrow_tile(pt.t) || kc_forced) return {false, pt};
     const GemmPlan pd = plan_gemm(M, g.C, Kb, z, 1, true, kg);
     const bool pd_ok = pd.t.wr * pd.t.wc * pd.t.kg == 8 && pt.splits == 1 && !kc_only(pd.t);
@@ -1950,31 +2049,50 @@ int64_t colsum_rows(const ConvGeom &g, const Tile &t) {
     return (((int64_t)g.N * g.H * g.W + t.bm - 1) / t.bm) * colsum_waves(t);
 }
 
+// dy with its channels padded, when K is no multiple of 8
+size_t pad_dy_bytes(const ConvGeom &g, int ldk) {
+    return g.K % 8 == 0 ? 0 : al256((size_t)g.N * g.P * g.Q * ldk * sizeof(bf16));
+}
+int dgrad_ldk(const ConvGeom &g) { return g.K % 8 == 0 ? g.K : pad_steps(g, g.K); }
+// K padded (the pitch of the dy that the kernels read), and C (what the plans see)
+ConvGeom padded_k(const ConvGeom &g) {
+    ConvGeom q = g;
+    q.K = dgrad_ldk(g);
+    return q;
+}
+bool ragged(const ConvGeom &g) { return g.K % 8 != 0 || g.C % 8 != 0; }
+// Whether K that is no multiple of 8 runs on a padded dy: it costs a pass over dy
+// in each gradient, and the 2-byte loads of igemm.hip cost more at every size
+// tried.  (16, 60, 57, 45), 100 filters of 3x3, step 2, us with every pass: input
+// gradient 62 there, 25 here; weight and bias gradients 68 there, 29 here.
+bool pad_dy_fits(const ConvGeom &g) {
+    const long ldk = dgrad_ldk(g);
+    return operand_fits((long)g.N * g.P * g.Q * ldk) && operand_fits(ldk * g.R * g.S * pad8(g.C));
+}
+
 // transposed filter (when used), then split-K partials indexed by dx pixel,
 // then (with_db, when the column sums ride along) their partial rows
 size_t dgrad_core_workspace(const ConvGeom &g, bool with_db) {
-    if (halo_dgrad_applies(g)) return al256((size_t)g.K * g.R * g.S * g.C * sizeof(bf16));   // the transposed filter
-    const DgradChoice dc = dgrad_choice(g);
+    const ConvGeom g8 = padded(padded_k(g));
+    if (halo_dgrad_applies(g8))   // the transposed filter; where C is padded, the bias and dx too
+        return al256((size_t)g8.K * g.R * g.S * g8.C * sizeof(bf16)) +
+               (g.C % 8 ? al256((size_t)g8.C * 2) + al256((size_t)g.N * g.H * g.W * g8.C * 2) : 0);
+    const DgradChoice dc = dgrad_choice(g8, ragged(g));
     const GemmPlan &p = dc.p;
-    size_t ws = dc.direct ? 0 : al256((size_t)g.K * g.R * g.S * g.C * sizeof(bf16));
+    size_t ws = dc.direct ? 0 : al256((size_t)g8.K * g.R * g.S * g.C * sizeof(bf16));
     if (p.splits > 1) ws += al256((size_t)p.splits * part_stride((int64_t)g.N * g.H * g.W * g.C) * sizeof(float));
-    if (with_db && colsum_rides(g, p)) ws += al256((size_t)colsum_rows(g, p.t) * g.K * sizeof(float));
+    if (with_db && !ragged(g) && colsum_rides(g, p)) ws += al256((size_t)colsum_rows(g, p.t) * g.K * sizeof(float));
     return ws;
 }
 
 size_t dgrad_workspace(const ConvGeom &g, bool with_db) {
-    if (g.K % 8 != 0) return 0;
-    if (g.C % 8 != 0) {
-        // block or pair packing (without a bias) or channel padding, whichever is larger
-        const size_t bq = block_applies(g) ? block_w_bytes(g) + block_x_bytes(g) + dgrad_core_workspace(blocked(g), false) : 0;
-        const size_t pq = std::max(bq, pair_applies(g) ? pair_w_bytes(g) + pair_x_bytes(g) + dgrad_core_workspace(paired(g), false) : 0);
-        // padded W, padded bias, padded dx, then the workspace of the padded
-        // contraction
-        const ConvGeom g8 = padded(g);
-        return std::max(pq, al256((size_t)g.K * g.R * g.S * g8.C * 2) + al256((size_t)g8.C * 2) +
-                                al256((size_t)g.N * g.H * g.W * g8.C * 2) + dgrad_core_workspace(g8, false));
-    }
-    return dgrad_core_workspace(g, with_db);
+    if (g.K % 8 != 0) return g.lean || !pad_dy_fits(g) ? 0 : pad_dy_bytes(g, dgrad_ldk(g)) + dgrad_core_workspace(g, false);
+    const size_t core = dgrad_core_workspace(g, with_db);
+    if (g.C % 8 == 0) return core;
+    // block or pair packing (without a bias) or the contraction itself, whichever is larger
+    const size_t bq = block_applies(g) ? block_w_bytes(g) + block_x_bytes(g) + dgrad_core_workspace(blocked(g), false) : 0;
+    const size_t pq = pair_applies(g) ? pair_w_bytes(g) + pair_x_bytes(g) + dgrad_core_workspace(paired(g), false) : 0;
+    return std::max({bq, pq, core});
 }
 
 // dx = input gradient (+ bias[c] per channel when bias is non-null: the
@@ -1984,8 +2102,14 @@ size_t dgrad_workspace(const ConvGeom &g, bool with_db) {
 int conv_dgrad(const ConvGeom &g, const void *dy, const void *w, const void *bias, void *dx, void *ws,
                hipStream_t st, void *db, bool *db_done) {
     if (db_done) *db_done = false;
-    if (g.K % 8 != 0) return -1;
-    if (g.C % 8 != 0 && block_applies(g) && !bias) {
+    const int K8 = dgrad_ldk(g);
+    if (g.K % 8 != 0) {
+        if (g.lean || !ws || !al16(ws) || !pad_dy_fits(g)) return -1;
+        const int err = pad_channels(pad_src(dy, (int64_t)g.N * g.P * g.Q, g.K, K8, ws), st);
+        if (err) return err;
+        dy = ws;
+        ws = static_cast<char *>(ws) + pad_dy_bytes(g, K8);
+    } else if (g.C % 8 != 0 && block_applies(g) && !bias) {
         if (!ws || !al16(ws)) return -1;
         char *wq = static_cast<char *>(ws);
         char *dxq = wq + block_w_bytes(g);
@@ -1995,8 +2119,7 @@ int conv_dgrad(const ConvGeom &g, const void *dy, const void *w, const void *bia
         err = conv_dgrad(blocked(g), dy, wq, nullptr, dxq, ws2, st, nullptr, nullptr);
         if (err) return err;   // -1: not applicable (the caller falls back), else a HIP error
         return unpack_blocks(g, dxq, dx, st);
-    }
-    if (g.C % 8 != 0 && pair_applies(g) && !bias) {
+    } else if (g.C % 8 != 0 && pair_applies(g) && !bias) {
         if (!ws || !al16(ws)) return -1;
         char *wq = static_cast<char *>(ws);
         char *dxq = wq + pair_w_bytes(g);
@@ -2007,66 +2130,69 @@ int conv_dgrad(const ConvGeom &g, const void *dy, const void *w, const void *bia
         if (err) return err;   // -1: not applicable (the caller falls back), else a HIP error
         return unpack_pairs(g, dxq, dx, st);
     }
-    if (g.C % 8 != 0) {
-        if (!ws || !al16(ws)) return -1;
-        const ConvGeom g8 = padded(g);
-        char *wp = static_cast<char *>(ws);
-        char *bp = wp + al256((size_t)g.K * g.R * g.S * g8.C * 2);
-        char *dxp = bp + al256((size_t)g8.C * 2);
-        char *ws2 = dxp + al256((size_t)g.N * g.H * g.W * g8.C * 2);
-        int err = pad_channels(w, (int64_t)g.K * g.R * g.S, g.C, wp, st);
-        if (!err && bias) err = pad_channels(bias, 1, g.C, bp, st);
-        if (err) return err;
-        err = conv_dgrad(g8, dy, wp, bias ? bp : nullptr, dxp, ws2, st, nullptr, nullptr);
-        if (err) return err;   // -1: not applicable (the caller falls back), else a HIP error
-        return crop_channels(dxp, (int64_t)g.N * g.H * g.W, g.C, dx, st);
-    }
-    if (!al16(dy) || !al16(w) || !al16(dx)) return -1;
-    if (!operand_fits((long)g.N * g.P * g.Q * g.K) || !operand_fits((long)g.K * g.R * g.S * g.C)) return -1;
-    if (halo_dgrad_applies(g)) {
+    const ConvGeom g8 = padded(padded_k(g));
+    const bool rag = ragged(g);
+    // rows of dx that are no whole vectors are stored at any alignment, and a
+    // ragged filter is read element by element
+    if (!al16(dy) || (!rag && !al16(w)) || (g.C % 8 == 0 && !al16(dx))) return -1;
+    if (!operand_fits((long)g.N * g.P * g.Q * K8) || !operand_fits((long)K8 * g.R * g.S * g8.C)) return -1;
+    if (halo_dgrad_applies(g8)) {
         // the correlation of dy with the flipped, transposed filter Wt[c][r][s][k]
         if (!ws || !al16(ws)) return -1;
         bf16 *wt = reinterpret_cast<bf16 *>(ws);
-        const int err = transpose_krsc(w, wt, g.K, g.R * g.S, g.C, st);
+        int err = transpose_filter(w, wt, g.K, g.R * g.S, g.C, K8, g8.C, st);
         if (err) return err;
+        void *out = dx;
+        if (g.C % 8 != 0) {
+            char *bp = static_cast<char *>(ws) + al256((size_t)K8 * g.R * g.S * g8.C * sizeof(bf16));
+            out = bp + al256((size_t)g8.C * 2);
+            if (bias) {
+                err = pad_channels(pad_src(bias, 1, g.C, g8.C, bp), st);
+                if (err) return err;
+                bias = bp;
+            }
+        }
         if (g.sh == 2)   // the four output phases
-            return run_halo((const bf16 *)dy, g.N, g.P, g.Q, wt, (const bf16 *)bias, g.C, g.R, g.S, g.ph, g.pw, false,
-                            (bf16 *)dx, g.H, g.W, st, 64, 1, true);
-        return run_halo((const bf16 *)dy, g.N, g.P, g.Q, wt, (const bf16 *)bias, g.C, g.R, g.S, g.R - 1 - g.ph,
-                        g.S - 1 - g.pw, true, (bf16 *)dx, g.H, g.W, st);
+            err = run_halo((const bf16 *)dy, g.N, g.P, g.Q, wt, (const bf16 *)bias, g8.C, g.R, g.S, g.ph, g.pw, false,
+                           (bf16 *)out, g.H, g.W, st, 64, 1, true);
+        else
+            err = run_halo((const bf16 *)dy, g.N, g.P, g.Q, wt, (const bf16 *)bias, g8.C, g.R, g.S, g.R - 1 - g.ph,
+                           g.S - 1 - g.pw, true, (bf16 *)out, g.H, g.W, st);
+        if (err || g.C % 8 == 0) return err;
+        return crop_channels(out, (int64_t)g.N * g.H * g.W, g.C, dx, st);
     }
-    const DgradChoice dc = dgrad_choice(g);
+    const DgradChoice dc = dgrad_choice(g8, rag);
     const bool direct = dc.direct;
     const GemmPlan &p = dc.p;
     if ((!direct || p.splits > 1) && (!ws || !al16(ws))) return -1;
     char *wsc = static_cast<char *>(ws);
     bf16 *wt = direct ? nullptr : reinterpret_cast<bf16 *>(wsc);
     float *part = nullptr;
-    if (p.splits > 1) part = reinterpret_cast<float *>(wsc + (direct ? 0 : al256((size_t)g.K * g.R * g.S * g.C * sizeof(bf16))));
+    if (p.splits > 1) part = reinterpret_cast<float *>(wsc + (direct ? 0 : al256((size_t)K8 * g.R * g.S * g.C * sizeof(bf16))));
     Args a{};
-    a.a = (const bf16 *)dy; a.b = direct ? (const bf16 *)w : wt; a.c = (bf16 *)dx; a.g = g;
+    a.a = (const bf16 *)dy; a.b = direct ? (const bf16 *)w : wt; a.c = (bf16 *)dx; a.g = g; a.g.K = K8;
     a.bias = (const bf16 *)bias;
     const int Hb = (g.H + g.sh - 1) / g.sh, Wb = (g.W + g.sw - 1) / g.sw;
     a.M = g.N * Hb * Wb; a.N = g.C;
-    a.K = ((g.R + g.sh - 1) / g.sh) * ((g.S + g.sw - 1) / g.sw) * g.K;
+    a.K = ((g.R + g.sh - 1) / g.sh) * ((g.S + g.sw - 1) / g.sw) * K8;
     if (a.M == 0 || a.N == 0) return 0;
     if (!direct) {
-        const int err = transpose_krsc(w, wt, g.K, g.R * g.S, g.C, st);
+        const int err = transpose_filter(w, wt, g.K, g.R * g.S, g.C, K8, g.C, st);
         if (err) return err;
     }
     a.ntm = (a.M + p.t.bm - 1) / p.t.bm; a.ntn = (a.N + p.t.bn - 1) / p.t.bn;
     a.splits = p.splits; a.k_split = p.k_split;
-    a.a_bytes = bytes_of((long)g.N * g.P * g.Q * g.K);
-    a.b_bytes = bytes_of((long)g.K * g.R * g.S * g.C);
+    a.a_bytes = bytes_of((long)g.N * g.P * g.Q * K8);
+    a.b_bytes = bytes_of((long)K8 * g.R * g.S * g.C);
     const int64_t n = (int64_t)g.N * g.H * g.W * g.C;
     if (p.splits > 1) {
         a.part = part;
         a.part_stride = part_stride(n);
         a.c = nullptr;
     }
-    const bool cs = db && !bias && colsum_rides(g, p);
+    const bool cs = db && !bias && !rag && colsum_rides(g, p);
     if (cs) {
-        a.cspart = reinterpret_cast<float *>(wsc + (direct ? 0 : al256((size_t)g.K * g.R * g.S * g.C * sizeof(bf16))));
+        a.cspart = reinterpret_cast<float *>(wsc + (direct ? 0 : al256((size_t)K8 * g.R * g.S * g.C * sizeof(bf16))));
         a.cs_cw = (g.K + a.ntn - 1) / a.ntn;
         a.cs_cw = (a.cs_cw + 7) / 8 * 8;
     }
@@ -2078,12 +2204,12 @@ int conv_dgrad(const ConvGeom &g, const void *dy, const void *w, const void *bia
         a.N = tsp.n1;
         a.ldc = g.C;
         a.ntn = (a.N + p.t.bn - 1) / p.t.bn;
-        a2.b += direct ? (size_t)tsp.n1 : (size_t)tsp.n1 * g.K;
+        a2.b += direct ? (size_t)tsp.n1 : (size_t)tsp.n1 * K8;
         a2.c += tsp.n1;
         if (a2.bias) a2.bias += tsp.n1;
         a2.N = g.C - tsp.n1;
         a2.ldc = g.C;
-        a2.b_bytes = direct ? bytes_of((long)g.K * g.C - tsp.n1) : bytes_of((long)a2.N * g.K);
+        a2.b_bytes = direct ? bytes_of((long)K8 * g.C - tsp.n1) : bytes_of((long)a2.N * K8);
         a2.ntm = (a2.M + tsp.p2.t.bm - 1) / tsp.p2.t.bm;
         a2.ntn = (a2.N + tsp.p2.t.bn - 1) / tsp.p2.t.bn;
         a2.k_split = tsp.p2.k_split;
@@ -2097,7 +2223,7 @@ int conv_dgrad(const ConvGeom &g, const void *dy, const void *w, const void *bia
     }
     const dim3 grid(a.ntm * a.ntn, 1, g.sh * g.sw * p.splits);
     int err = direct ? go_mode<kDgradN>(p.t, a, grid, unit_geom(g), st)
-                     : go_mode<kDgrad>(p.t, a, grid, unit_geom(g), st, ts_dgrad(g));
+                     : go_mode<kDgrad>(p.t, a, grid, unit_geom(g), st, ts_dgrad(g8));
     if (err) return err;
     if (cs) {
         err = launch_colsum_finalize(kBF16, a.cspart, (int)colsum_rows(g, p.t), g.K, db, st);
@@ -2108,16 +2234,17 @@ int conv_dgrad(const ConvGeom &g, const void *dy, const void *w, const void *bia
     return reduce_partials(part, p.splits, n, a.part_stride, (bf16 *)dx, (const bf16 *)bias, g.C, st);
 }
 
-bool wgrad_applies(const ConvGeom &g) { return g.K % 8 == 0; }
+bool wgrad_applies(const ConvGeom &g) { return g.K % 8 == 0 || (!g.lean && pad_dy_fits(g)); }
 
-size_t wgrad_workspace(const ConvGeom &g, bool with_db) {
+// padded dy (rows of roundup(K, 8)), then as wgrad_core_workspace
+size_t wgrad_core_workspace(const ConvGeom &g, bool with_db) {
     if (g.C % 8 != 0 && pair_applies(g))
-        return pair_x_bytes(g) + pair_w_bytes(g) + wgrad_workspace(paired(g), with_db);
+        return pair_x_bytes(g) + pair_w_bytes(g) + wgrad_core_workspace(paired(g), with_db);
     if (g.C % 8 != 0) {
         // padded x, padded dW, then the workspace of the padded contraction
         const ConvGeom g8 = padded(g);
         return al256((size_t)g.N * g.H * g.W * g8.C * 2) + al256((size_t)g.K * g.R * g.S * g8.C * 2) +
-               wgrad_workspace(g8, with_db);
+               wgrad_core_workspace(g8, with_db);
     }
     WgradPlan p = wgrad_plan(g);
     size_t ws = 0;
@@ -2126,16 +2253,23 @@ size_t wgrad_workspace(const ConvGeom &g, bool with_db) {
     return ws;
 }
 
-int conv_wgrad(const ConvGeom &g, const void *dy, const void *x, void *dw, void *db, void *ws, hipStream_t st) {
-    if (!wgrad_applies(g)) return -1;
+size_t wgrad_workspace(const ConvGeom &g, bool with_db) {
+    return pad_dy_bytes(g, pad8(g.K)) + wgrad_core_workspace(g, with_db);
+}
+
+// dy has rows of roundup(K, 8) channels; `crop`: dw's real channels, where x (and
+// g.C) is padded (0: all of them); `pad`: a dy still to be padded into place
+int wgrad_core(const ConvGeom &g, const void *dy, const void *x, void *dw, void *db, void *ws, hipStream_t st,
+               int crop = 0, const PadSrc &pad = PadSrc{}) {
     if (g.C % 8 != 0 && pair_applies(g)) {
         if (!ws || !al16(ws) || !al16(dy)) return -1;
         char *xq = static_cast<char *>(ws);
         char *dwq = xq + pair_x_bytes(g);
         char *ws2 = dwq + pair_w_bytes(g);
         int err = pack_pairs(g, x, xq, st);
+        if (!err) err = pad_channels(pad, st);
         if (err) return err;
-        err = conv_wgrad(paired(g), dy, xq, dwq, db, ws2, st);
+        err = wgrad_core(paired(g), dy, xq, dwq, db, ws2, st);
         if (err) return err;   // -1: not applicable (the caller falls back), else a HIP error
         return unpack_pair_filter(g, dwq, dw, st);
     }
@@ -2145,19 +2279,24 @@ int conv_wgrad(const ConvGeom &g, const void *dy, const void *x, void *dw, void 
         char *xp = static_cast<char *>(ws);
         char *dwp = xp + al256((size_t)g.N * g.H * g.W * g8.C * 2);
         char *ws2 = dwp + al256((size_t)g.K * g.R * g.S * g8.C * 2);
-        int err = pad_channels(x, (int64_t)g.N * g.H * g.W, g.C, xp, st);
+        int err = pad_channels(pad_src(x, (int64_t)g.N * g.H * g.W, g.C, g8.C, xp), pad, st);
         if (err) return err;
-        err = conv_wgrad(g8, dy, xp, dwp, db, ws2, st);
-        if (err) return err;   // -1: not applicable (the caller falls back), else a HIP error
+        // a split contraction's reduction leaves the padding out itself
+        const bool split = wgrad_plan(g8).splits > 1;
+        err = wgrad_core(g8, dy, xp, split ? dw : dwp, db, ws2, st, split ? g.C : 0);
+        if (err || split) return err;   // -1: not applicable (the caller falls back), else a HIP error
         return crop_channels(dwp, (int64_t)g.K * g.R * g.S, g.C, dw, st);
     }
-    if (!al16(dy) || !al16(x) || !al16(dw)) return -1;
-    if (!operand_fits((long)g.N * g.P * g.Q * g.K) || !operand_fits((long)g.N * g.H * g.W * g.C)) return -1;
+    if (!al16(dy) || !al16(x) || (!crop && !al16(dw))) return -1;
+    const int K8 = pad8(g.K);
+    if (!operand_fits((long)g.N * g.P * g.Q * K8) || !operand_fits((long)g.N * g.H * g.W * g.C)) return -1;
     WgradPlan p = wgrad_plan(g);
     Args a{};
-    a.a = (const bf16 *)dy; a.b = (const bf16 *)x; a.g = g;
+    a.a = (const bf16 *)dy; a.b = (const bf16 *)x; a.g = g; a.g.K = K8;
     a.M = g.K; a.N = g.R * g.S * g.C; a.K = g.N * g.P * g.Q;
     if (a.M == 0 || a.N == 0) return 0;
+    int err = pad_channels(pad, st);
+    if (err) return err;
     a.ntm = (a.M + p.t.bm - 1) / p.t.bm; a.ntn = (a.N + p.t.bn - 1) / p.t.bn;
     a.splits = p.splits; a.k_split = p.k_split;
     float *wsf = static_cast<float *>(ws);
@@ -2171,18 +2310,33 @@ int conv_wgrad(const ConvGeom &g, const void *dy, const void *x, void *dw, void 
         a.c = (bf16 *)dw;
     }
     a.dbpart = db ? wsf + used : nullptr;
-    a.a_bytes = bytes_of((long)g.N * g.P * g.Q * g.K);
+    a.a_bytes = bytes_of((long)g.N * g.P * g.Q * K8);
     a.b_bytes = bytes_of((long)g.N * g.H * g.W * g.C);
-    int err = go_mode<kWgrad>(p.t, a, dim3(a.ntm * a.ntn, 1, p.splits), unit_geom(g), st, true);
+    err = go_mode<kWgrad>(p.t, a, dim3(a.ntm * a.ntn, 1, p.splits), unit_geom(g), st, true);
     if (err) return err;
     if (p.splits > 1 || db) {
         const int64_t n = p.splits > 1 ? (int64_t)a.M * a.N : 0;
         const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>((n / 4 + 255) / 256, 2048));
-        hipLaunchKernelGGL(reduce_kernel, dim3(blocks), dim3(256), 0, st, (const float *)a.part, p.splits, n, n,
-                           (bf16 *)dw, (const float *)a.dbpart, db ? a.M : 0, (bf16 *)db, (const bf16 *)nullptr, 1);
+        if (crop)
+            hipLaunchKernelGGL(reduce_kernel<true>, dim3(blocks), dim3(256), 0, st, (const float *)a.part, p.splits, n,
+                               n, (bf16 *)dw, (const float *)a.dbpart, db ? a.M : 0, (bf16 *)db, (const bf16 *)nullptr,
+                               1, g.C, crop);
+        else
+            hipLaunchKernelGGL(reduce_kernel<false>, dim3(blocks), dim3(256), 0, st, (const float *)a.part, p.splits, n,
+                               n, (bf16 *)dw, (const float *)a.dbpart, db ? a.M : 0, (bf16 *)db, (const bf16 *)nullptr,
+                               1);
         err = (int)hipGetLastError();
     }
     return err;
+}
+
+int conv_wgrad(const ConvGeom &g, const void *dy, const void *x, void *dw, void *db, void *ws, hipStream_t st) {
+    if (!wgrad_applies(g)) return -1;
+    if (g.K % 8 == 0) return wgrad_core(g, dy, x, dw, db, ws, st);
+    if (!ws || !al16(ws)) return -1;
+    const int K8 = pad8(g.K);
+    return wgrad_core(g, ws, x, dw, db, static_cast<char *>(ws) + pad_dy_bytes(g, K8), st, 0,
+                      pad_src(dy, (int64_t)g.N * g.P * g.Q, g.K, K8, ws));
 }
 
 // ---------------------------------------------------------------- three dimensions
@@ -2406,7 +2560,7 @@ int conv3d_wgrad(const Conv3dGeom &q, const void *dv, const void *u, void *dw, v
     if (!err && (p.splits > 1 || db)) {
         const int64_t n = p.splits > 1 ? (int64_t)a.M * a.N : 0;
         const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>((n / 4 + 255) / 256, 2048));
-        hipLaunchKernelGGL(reduce_kernel, dim3(blocks), dim3(256), 0, st, (const float *)a.part, p.splits, n, n, (bf16 *)dw,
+        hipLaunchKernelGGL(reduce_kernel<false>, dim3(blocks), dim3(256), 0, st, (const float *)a.part, p.splits, n, n, (bf16 *)dw,
                            (const float *)a.dbpart, db ? a.M : 0, (bf16 *)db, (const bf16 *)nullptr, 1);
         err = (int)hipGetLastError();
     }

@@ -20,6 +20,11 @@
 //
 // The fully-connected layer is the 1x1 / stride 1 / pad 0 case (UNIT).
 //
+// These are the kernels of last resort: operands past 32-bit byte offsets, bf16
+// tensors off 16-byte alignment, and bf16 channel counts that are no multiples
+// of 8 where there is no workspace for padded copies.  All else runs in
+// gemm_bf16.hip, gemm_f32.hip and few_f32.hip.
+//
 // Block: 256 threads = 4 waves in a 2x2 grid; block tile BM x BN, K step BK,
 // two LDS stages (global loads of tile k+1 overlap the MFMAs of tile k).
 // LDS holds both operands as [row][k] (k contiguous, padded rows) so each
