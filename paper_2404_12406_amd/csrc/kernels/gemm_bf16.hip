@@ -1060,24 +1060,45 @@ __global__ __launch_bounds__(256) void crop_channels_kernel(const bf16 *__restri
 // Sum split-K partials (and fused bias-gradient partials) to bf16; with a
 // bias, out[i] also gets bias[i % ncol] (added in fp32 before the rounding).
 // CROP: rows of C8 (a multiple of 4) partials keep their first C elements.
-template <bool CROP>
+// A block owns 256 / G columns of four; its G thread groups take every G-th
+// split and meet in LDS, in a fixed order.  Bound by load latency where the
+// output is small: few waves, each a chain of splits / (6 G) round trips
+// (reduce_groups() has the rule and what it measured).
+template <bool CROP, int G>
 __global__ __launch_bounds__(256) void reduce_kernel(const float *__restrict__ part, int splits, int64_t n,
                                                      int64_t pstride, bf16 *__restrict__ out, const float *__restrict__ dbpart,
                                                      int M, bf16 *__restrict__ db, const bf16 *__restrict__ bias,
-                                                     int ncol, int C8 = 4, int C = 4) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+                                                     int ncol, int C8, int C) {
+    constexpr int COLS = 256 / G;
+    __shared__ floatx4 red[G > 1 ? G : 1][G > 1 ? COLS : 1];
+    const int col = threadIdx.x % COLS, grp = threadIdx.x / COLS;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x, cstride = (int64_t)gridDim.x * COLS;
     const int64_t nv = n / 4;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nv; i += stride) {
-        floatx4 s = *reinterpret_cast<const floatx4 *>(part + 4 * i);
-        int z = 1;
-        for (; z + 6 <= splits; z += 6) {   // six loads in flight, summed in their order
-            floatx4 t[6];
+    for (int64_t i0 = (int64_t)blockIdx.x * COLS; i0 < nv; i0 += cstride) {   // (the same for the block: it meets inside)
+        const int64_t i = i0 + col;
+        floatx4 s = {0.f, 0.f, 0.f, 0.f};
+        if (i < nv && grp < splits) {
+            s = *reinterpret_cast<const floatx4 *>(part + (int64_t)grp * pstride + 4 * i);
+            int z = grp + G;
+            for (; z + 5 * G < splits; z += 6 * G) {   // six loads in flight, summed in their order
+                floatx4 t[6];
 #pragma unroll
-            for (int u = 0; u < 6; ++u) t[u] = *reinterpret_cast<const floatx4 *>(part + (int64_t)(z + u) * pstride + 4 * i);
+                for (int u = 0; u < 6; ++u)
+                    t[u] = *reinterpret_cast<const floatx4 *>(part + (int64_t)(z + u * G) * pstride + 4 * i);
 #pragma unroll
-            for (int u = 0; u < 6; ++u) s += t[u];
+                for (int u = 0; u < 6; ++u) s += t[u];
+            }
+            for (; z < splits; z += G) s += *reinterpret_cast<const floatx4 *>(part + (int64_t)z * pstride + 4 * i);
         }
-        for (; z < splits; ++z) s += *reinterpret_cast<const floatx4 *>(part + (int64_t)z * pstride + 4 * i);
+        if constexpr (G > 1) {
+            red[grp][col] = s;
+            __syncthreads();
+            if (grp == 0)
+#pragma unroll
+                for (int q = 1; q < G; ++q) s += red[q][col];
+            __syncthreads();
+        }
+        if (grp != 0 || i >= nv) continue;
         if (bias) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) s[e] += (float)bias[(4 * i + e) % ncol];
@@ -1100,10 +1121,20 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float *__restrict__ p
         out[i] = (bf16)s;
     }
     if (dbpart) {
-        for (int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; m < M; m += stride) {
+        for (int64_t m0 = (int64_t)blockIdx.x * COLS; m0 < M; m0 += cstride) {
+            const int64_t m = m0 + col;
             float s = 0.f;
-            for (int z = 0; z < splits; ++z) s += dbpart[(int64_t)z * M + m];
-            db[m] = (bf16)s;
+            if (m < M)
+                for (int z = grp; z < splits; z += G) s += dbpart[(int64_t)z * M + m];
+            if constexpr (G > 1) {
+                red[grp][col][0] = s;
+                __syncthreads();
+                if (grp == 0)
+#pragma unroll
+                    for (int q = 1; q < G; ++q) s += red[q][col][0];
+                __syncthreads();
+            }
+            if (grp == 0 && m < M) db[m] = (bf16)s;
         }
     }
 }
@@ -1714,14 +1745,33 @@ WgradPlan wgrad_plan(const ConvGeom &g) {
 
 // Each returns -1 when the fast path does not apply, else a hipError_t.
 
+// Thread groups that share a column's splits: four where the columns fill no
+// block a CU and there are two splits a group, so that the loads of a small
+// output come from more waves.  One group -> four, us: 57,600 floats of 19
+// splits 7.0 -> 4.4, 110,592 of 36 11.6 -> 5.9 (2.7 TB/s).  Larger outputs have
+// the waves already: 589,824 floats of 7 splits take 6.0 with one (2.8 TB/s).
+int reduce_groups(int splits, int64_t n) { return splits >= 8 && n / 4 < (int64_t)kCUs * 256 ? 4 : 1; }
+
+// reduce_kernel over n floats of `splits` partials and M bias-gradient columns
+// (crop: rows of C8 partials keep their first `crop` elements).
+int launch_reduce(const float *part, int splits, int64_t n, int64_t pstride, bf16 *out, const float *dbpart, int M, bf16 *db,
+                  const bf16 *bias, int ncol, int C8, int crop, int most, hipStream_t st) {
+    const int groups = reduce_groups(splits, n), cols = 256 / groups;
+    const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>((std::max<int64_t>(n / 4, dbpart ? M : 0) + cols - 1) / cols, most));
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, st, part, splits, n, pstride, out, dbpart, M, db, bias, ncol, C8,
+                           crop);
+    };
+    if (crop) groups > 1 ? go(reduce_kernel<true, 4>) : go(reduce_kernel<true, 1>);
+    else groups > 1 ? go(reduce_kernel<false, 4>) : go(reduce_kernel<false, 1>);
+    return (int)hipGetLastError();
+}
+
 // Sum `splits` partial arrays of n floats (pstride apart) to bf16 `out`,
 // adding bias[i % ncol] when bias is given.
 int reduce_partials(const float *part, int splits, int64_t n, int64_t pstride, bf16 *out, const bf16 *bias, int ncol,
                     hipStream_t st) {
-    const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>((n / 4 + 255) / 256, 4096));
-    hipLaunchKernelGGL(reduce_kernel<false>, dim3(blocks), dim3(256), 0, st, part, splits, n, pstride, out,
-                       (const float *)nullptr, 0, (bf16 *)nullptr, bias, ncol);
-    return (int)hipGetLastError();
+    return launch_reduce(part, splits, n, pstride, out, nullptr, 0, nullptr, bias, ncol, 4, 0, 4096, st);
 }
 
 // ---------------------------------------------------------------- halo convolution (host)
@@ -2316,16 +2366,8 @@ int wgrad_core(const ConvGeom &g, const void *dy, const void *x, void *dw, void 
     if (err) return err;
     if (p.splits > 1 || db) {
         const int64_t n = p.splits > 1 ? (int64_t)a.M * a.N : 0;
-        const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>((n / 4 + 255) / 256, 2048));
-        if (crop)
-            hipLaunchKernelGGL(reduce_kernel<true>, dim3(blocks), dim3(256), 0, st, (const float *)a.part, p.splits, n,
-                               n, (bf16 *)dw, (const float *)a.dbpart, db ? a.M : 0, (bf16 *)db, (const bf16 *)nullptr,
-                               1, g.C, crop);
-        else
-            hipLaunchKernelGGL(reduce_kernel<false>, dim3(blocks), dim3(256), 0, st, (const float *)a.part, p.splits, n,
-                               n, (bf16 *)dw, (const float *)a.dbpart, db ? a.M : 0, (bf16 *)db, (const bf16 *)nullptr,
-                               1);
-        err = (int)hipGetLastError();
+        err = launch_reduce(a.part, p.splits, n, n, (bf16 *)dw, a.dbpart, db ? a.M : 0, (bf16 *)db, nullptr, 1, g.C, crop, 2048,
+                            st);
     }
     return err;
 }
@@ -2559,10 +2601,7 @@ int conv3d_wgrad(const Conv3dGeom &q, const void *dv, const void *u, void *dw, v
     int err = go3<kWgrad>(p.t, a, dim3(a.ntm * a.ntn, 1, p.splits), st);
     if (!err && (p.splits > 1 || db)) {
         const int64_t n = p.splits > 1 ? (int64_t)a.M * a.N : 0;
-        const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>((n / 4 + 255) / 256, 2048));
-        hipLaunchKernelGGL(reduce_kernel<false>, dim3(blocks), dim3(256), 0, st, (const float *)a.part, p.splits, n, n, (bf16 *)dw,
-                           (const float *)a.dbpart, db ? a.M : 0, (bf16 *)db, (const bf16 *)nullptr, 1);
-        err = (int)hipGetLastError();
+        err = launch_reduce(a.part, p.splits, n, n, (bf16 *)dw, a.dbpart, db ? a.M : 0, (bf16 *)db, nullptr, 1, 4, 0, 2048, st);
     }
     return err;
 }
