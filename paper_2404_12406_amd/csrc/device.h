@@ -14,11 +14,15 @@ enum Dtype : int { kF32 = 0, kBF16 = 1 };
 // Convolution geometry.  Activations are NHWC, filters KRSC, all dense.
 // The fully-connected layer is the special case H = W = R = S = P = Q = 1,
 // stride 1, pad 0 (x[M,K_in] = NHWC with N = M, C = K_in; W[N_out,K_in] = KRSC).
-struct ConvGeom {
+struct ConvDims {
     int N, C, H, W;   // input
     int K, R, S;      // filters
     int P, Q;         // output extent
     int sh, sw, ph, pw;
+};
+
+// The geometry and how a layer is to run; kernels take the dimensions alone.
+struct ConvGeom : ConvDims {
     // the launchers take no more workspace than the passes cannot do without (fp32
     // forwards and input gradients: none, they run unsplit): what the runtime falls
     // back to where the workspace cannot be had

@@ -65,7 +65,7 @@ struct Args {
     int64_t part_stride;  // FWD/WGRAD: M*N; DGRAD: N*H*W*C (partials indexed by dx pixel)
     const bf16 *bias;     // FWD / DGRAD per-column bias (nullptr: none; DGRAD: the
                           // transposed convolution's forward)
-    ConvGeom g;
+    ConvDims g;
     int M, N, K;          // GEMM extents (DGRAD: bounds over phases)
     int ntm, ntn;
     int ldc;              // bf16 output row stride in elements (0: N); a launch that covers
@@ -82,7 +82,7 @@ struct Phase {
     int fh, fw, h0, w0, Hp, Wp, Rp, Sp, dh, dw;
 };
 
-__device__ __forceinline__ Phase make_phase(const ConvGeom &g, int z) {
+__device__ __forceinline__ Phase make_phase(const ConvDims &g, int z) {
     Phase f;
     f.fh = z / g.sw;
     f.fw = z % g.sw;
