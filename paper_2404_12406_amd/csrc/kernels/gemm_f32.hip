@@ -623,13 +623,17 @@ double est_us(const TileInfo &t, int64_t M, int64_t N, int64_t K, int z, int spl
     return us;
 }
 
+// floats between the partials of two splits: whole vectors
+int64_t part_stride(int64_t elems) { return (elems + 3) / 4 * 4; }
+
+// `cap_bytes`: what the partials, part_stride(out_elems) apart, may take
 Plan plan(int mode, int64_t M, int64_t N, int64_t K, int z, int64_t out_elems, int64_t cap_bytes) {
     Plan best{0, 1, 0};
     double bt = 1e300;
     for (int ti = 0; ti < kNumTiles; ++ti) {
         const TileInfo &t = kTiles[ti];
         if (t.bm == 32 && mode != kWgrad) continue;   // rows are pixels there: never few
-        const int64_t most = std::max<int64_t>(1, std::min<int64_t>(K / (4 * BK), cap_bytes / std::max<int64_t>(1, 4 * out_elems)));
+        const int64_t most = std::max<int64_t>(1, std::min<int64_t>(K / (4 * BK), cap_bytes / std::max<int64_t>(1, 4 * part_stride(out_elems))));
         for (int64_t sp = 1; sp <= std::min<int64_t>(most, 1024); sp += sp < 16 ? 1 : sp / 8) {
             const double us = est_us(t, M, N, K, z, (int)sp);
             if (us < bt * 0.999) {
@@ -646,7 +650,6 @@ Plan plan(int mode, int64_t M, int64_t N, int64_t K, int z, int64_t out_elems, i
 }
 
 bool al16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
-int64_t part_stride(int64_t elems) { return (elems + 3) / 4 * 4; }
 size_t part_bytes(const Plan &p, int64_t elems) {
     return p.splits > 1 ? (size_t)p.splits * part_stride(elems) * sizeof(float) : 0;
 }
@@ -748,13 +751,17 @@ int run(const Plan &p, bool vec, Args &a, int z, int64_t out_elems, const float 
 
 }  // namespace
 
+// Partial rows of the few-channel weight gradient, two blocks a CU; 0: the GEMM
+// takes it.
+static int few_rows(const ConvGeom &g, size_t cap) {
+    const int64_t rows = std::min<int64_t>(512, (int64_t)cap / (part_stride(w_elems(g)) * 4));
+    return rows >= 64 && few::wgrad_applies(g) ? (int)rows : 0;
+}
+
 // Workspace in bytes (split partials).  A forward or input gradient that is
 // given no workspace runs unsplit.
 size_t fwd_workspace(const ConvGeom &g) { return geom_ok(g) ? part_bytes(fwd_plan(g), y_elems(g)) : 0; }
 size_t dgrad_workspace(const ConvGeom &g) { return geom_ok(g) ? part_bytes(dgrad_plan(g), x_elems(g)) : 0; }
-size_t wgrad_workspace(const ConvGeom &g, size_t cap) {
-    return geom_ok(g) ? part_bytes(wgrad_plan(g, (int64_t)cap), w_elems(g)) : 0;
-}
 
 // Each returns -1 when an operand is too large for 32-bit byte offsets (the
 // general kernel takes it), else a hipError_t.
@@ -792,15 +799,35 @@ int conv_wgrad(const ConvGeom &g, const void *dy, const void *x, void *dw, void 
     a.a = (const float *)dy; a.b = (const float *)x; a.g = g;
     a.M = g.K; a.N = g.R * g.S * g.C; a.K = g.N * g.P * g.Q;
     if (a.M == 0 || a.N == 0) return 0;
-    const int64_t row = part_stride(w_elems(g));
-    const int rows = (int)std::min<int64_t>(512, (int64_t)cap / (row * 4));   // two blocks a CU
-    if (rows >= 64 && few::wgrad_applies(g) && ws && al16(ws)) {
-        const int err = few::wgrad_parts(g, dy, x, static_cast<float *>(ws), row, rows, st);
+    const int rows = few_rows(g, cap);
+    if (rows && ws && al16(ws)) {
+        const int err = few::wgrad_parts(g, dy, x, static_cast<float *>(ws), part_stride(w_elems(g)), rows, st);
         return err ? err : reduce(static_cast<const float *>(ws), rows, w_elems(g), nullptr, 1, (float *)dw, st);
     }
     const Plan p = wgrad_plan(g, (int64_t)cap);
     if (p.splits > 1 && (!ws || !al16(ws))) return (int)hipErrorInvalidValue;
     return run<kWgrad>(p, g.K % 4 == 0 && g.C % 4 == 0 && al16(dy) && al16(x), a, 1, w_elems(g), nullptr, (float *)dw, ws, st);
+}
+
+// What a pass (0 forward, 1 input gradient, 2 weight gradient) lays out: out =
+// {splits, bytes of their partials, blocks along grid z}; -1: it is not taken.
+int plan_info(int pass, const ConvGeom &g, size_t cap, int64_t out[3]) {
+    if (!geom_ok(g)) return -1;
+    const int z = pass == kDgrad ? g.sh * g.sw : 1;
+    const int64_t elems = pass == kFwd ? y_elems(g) : pass == kDgrad ? x_elems(g) : w_elems(g);
+    const bool few = pass == kFwd ? few::fwd_applies(g, nullptr) : pass == kDgrad ? few::dgrad_applies(g, nullptr) : false;
+    const int rows = pass == kWgrad && elems > 0 ? few_rows(g, cap) : 0;
+    if (few || rows) {
+        out[0] = few ? 1 : rows;
+        out[1] = few ? 0 : rows * part_stride(elems) * 4;
+        out[2] = 1;
+        return 0;
+    }
+    const Plan p = pass == kFwd ? fwd_plan(g) : pass == kDgrad ? dgrad_plan(g) : wgrad_plan(g, (int64_t)cap);
+    out[0] = p.splits;
+    out[1] = (int64_t)part_bytes(p, elems);
+    out[2] = (int64_t)z * p.splits;
+    return 0;
 }
 
 }  // namespace f32g
