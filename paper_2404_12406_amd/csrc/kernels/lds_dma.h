@@ -30,7 +30,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *p, uint32_t b
 //  * block_sync() tells the compiler that LDS may have changed, so no LDS
 //    value read before a barrier is reused after it.
 // M0 is reserved by the compiler and no other instruction of these kernels
-// reads it.
+// reads it.  A load that writes LDS needs one wait state after a scalar write of
+// M0; the compiler puts it there for the builtin but does not look inside
+// inline assembly, so the assembly forms carry their own s_nop.
 // (The offset is computed into a named value first: passing a conditional
 // expression straight into the builtin inside a kernel template makes the
 // host pass drop the kernel's launch stub.)
@@ -38,7 +40,7 @@ template <bool ASM>
 __device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, char *lds, uint32_t off) {
     if constexpr (ASM) {
         const uint32_t base = (uint32_t)(uintptr_t)(lds_void_t *)lds;
-        asm volatile("s_mov_b32 m0, %1\n\tbuffer_load_dwordx4 %0, %2, 0 offen lds" ::"v"(off), "s"(base), "s"(r));
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %2, 0 offen lds" ::"v"(off), "s"(base), "s"(r));
     } else {
         __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t *)lds, 16, off, 0, 0, 0);
     }
@@ -48,11 +50,11 @@ __device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, char *lds, uint3
 // 4-byte sibling (lane l's dword lands at lds + 4 l).
 __device__ __forceinline__ void dma16s(__amdgpu_buffer_rsrc_t r, char *lds, uint32_t off, uint32_t soff) {
     const uint32_t base = (uint32_t)(uintptr_t)(lds_void_t *)lds;
-    asm volatile("s_mov_b32 m0, %1\n\tbuffer_load_dwordx4 %0, %2, %3 offen lds" ::"v"(off), "s"(base), "s"(r), "s"(soff));
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %2, %3 offen lds" ::"v"(off), "s"(base), "s"(r), "s"(soff));
 }
 __device__ __forceinline__ void dma4s(__amdgpu_buffer_rsrc_t r, char *lds, uint32_t off, uint32_t soff) {
     const uint32_t base = (uint32_t)(uintptr_t)(lds_void_t *)lds;
-    asm volatile("s_mov_b32 m0, %1\n\tbuffer_load_dword %0, %2, %3 offen lds" ::"v"(off), "s"(base), "s"(r), "s"(soff));
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dword %0, %2, %3 offen lds" ::"v"(off), "s"(base), "s"(r), "s"(soff));
 }
 
 // Workgroup barrier; with untracked LDS-DMA loads it is also a compiler-level

@@ -10,9 +10,16 @@ are checked on every kernel:
 * no dispatch-packet pointer: the compiler asks for it when a private array
   is promoted into LDS, and every wave then reads the workgroup size from the
   dispatch packet in host memory (it cost the GEMM epilogue 1-12 us a launch).
+
+And on their instructions:
+
+* a load into LDS never follows a write of M0 directly: the hardware needs one
+  wait state between them, which the compiler does not add in inline assembly.
 """
 import os
+import re
 import struct
+import subprocess
 
 import pytest
 
@@ -71,6 +78,32 @@ def _kernel_descriptors(elf):
     return kds
 
 
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+
+
+@pytest.fixture(scope="module")
+def listings(tmp_path_factory):
+    """{kernel name: its instructions, in order} of the whole library."""
+    if not os.path.exists(L.LIB_PATH):
+        pytest.skip("libmemsave.so not built")
+    out = {}
+    for i, (_, elf) in enumerate(_code_objects(L.LIB_PATH)):
+        if not elf:
+            continue
+        path = tmp_path_factory.mktemp("co") / f"{i}.elf"
+        path.write_bytes(elf)
+        text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(path)], capture_output=True, text=True,
+                              check=True).stdout
+        body = None
+        for line in text.splitlines():
+            head = re.match(r"[0-9a-f]+ <(.+)>:$", line)
+            if head:
+                body = out.setdefault(head.group(1), [])
+            elif body is not None and line.startswith("\t"):
+                body.append(line.split("//")[0].strip())
+    return out
+
+
 @pytest.fixture(scope="module")
 def descriptors():
     if not os.path.exists(L.LIB_PATH):
@@ -100,3 +133,14 @@ def test_no_kernel_uses_scratch(descriptors):
 def test_no_kernel_reads_the_dispatch_packet(descriptors):
     bad = [k for k, d in descriptors.items() if struct.unpack_from("<H", d, KD_CODE_PROPERTIES)[0] & SGPR_DISPATCH_PTR]
     assert not bad, f"kernels that enable the dispatch pointer: {bad}"
+
+
+def test_loads_into_lds_keep_their_distance_from_m0(listings):
+    loads, bad = 0, []
+    for name, body in listings.items():
+        for before, ins in zip(body, body[1:]):
+            if re.match(r"(buffer|global|scratch)_load.*\blds\b", ins):
+                loads += 1
+                if re.match(r"s_\w+ m0,", before):
+                    bad.append((name, ins))
+    assert loads > 1000 and not bad, (loads, len(bad), bad[:3])
