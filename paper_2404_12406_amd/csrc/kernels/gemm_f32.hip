@@ -435,6 +435,8 @@ __global__ __launch_bounds__(256, OCC) void gemm_kernel(const Args P) {
     auto step = [&](auto stage_c, int kt) __attribute__((always_inline)) {
         constexpr int ST = decltype(stage_c)::value;
         g2::wait_vmcnt<0>();
+        g2::wait_lgkm0();         // this wave has read the other stage: the refills below are not
+                                  // tracked, so nothing else keeps them behind its reads
         g2::block_sync<true>();   // step kt has landed for every wave; the other stage is free
         const int k1 = k_begin + (kt + 1) * BK;
         if constexpr (UT && MODE != kWgrad) u_next();

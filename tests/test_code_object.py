@@ -14,7 +14,10 @@ are checked on every kernel:
 And on their instructions:
 
 * a load into LDS never follows a write of M0 directly: the hardware needs one
-  wait state between them, which the compiler does not add in inline assembly.
+  wait state between them, which the compiler does not add in inline assembly;
+* the step barrier of the fp32 GEMM waits for the wave's own LDS reads: the loads
+  that refill the stage behind it are in inline assembly, so the compiler does
+  not order them after those reads.
 """
 import os
 import re
@@ -144,3 +147,16 @@ def test_loads_into_lds_keep_their_distance_from_m0(listings):
                 if re.match(r"s_\w+ m0,", before):
                     bad.append((name, ins))
     assert loads > 1000 and not bad, (loads, len(bad), bad[:3])
+
+
+def test_float_gemm_barriers_wait_for_lds_reads(listings):
+    barriers, bad = 0, []
+    for name, body in listings.items():
+        if "f32g" not in name or "gemm_kernel" not in name:
+            continue
+        for before, ins in zip(body, body[1:]):
+            if ins == "s_barrier":
+                barriers += 1
+                if not (before.startswith("s_waitcnt") and "lgkmcnt(0)" in before and "vmcnt(0)" in before):
+                    bad.append((name, before))
+    assert barriers >= 36 and not bad, (barriers, len(bad), bad[:3])
