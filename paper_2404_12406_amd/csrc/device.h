@@ -25,7 +25,7 @@ struct ConvDims {
 struct ConvGeom : ConvDims {
     // the launchers take no more workspace than the passes cannot do without (fp32
     // forwards and input gradients: none, they run unsplit): what the runtime falls
-    // back to where the workspace cannot be had
+    // back to where the workspace cannot be had, and what it captures
     int lean = 0;
 };
 
@@ -146,8 +146,9 @@ int launch_copy4(int dtype, const void *src, const int64_t ext[4], const int64_t
 
 // Per-stream transient workspace (workspace.hip).  Returns null and sets
 // *err on failure: 1 unavailable, 2 another HIP error.  With *err negative on
-// entry the caller can do with less: where the buffer would have to grow while
-// the stream is being captured, nothing is allocated and *err is kWsCapture.
+// entry the caller can do with less: while the stream is being captured it gets
+// none, *err is kWsCapture, and the graph holds no buffer that a later call on
+// the stream may outgrow and free.
 constexpr int kWsCapture = 3;
 void *workspace_get(void *stream, size_t bytes, int *err);
 // Test hook: make the next `n` workspace growths fail.

@@ -630,6 +630,12 @@ Plan lean_plan(const Plan &pl) {
     return l;
 }
 
+// Whether that may be less: fp32 and channel counts that are not multiples of 8.
+bool has_lean(const Plan &pl) {
+    return (pl.kind == MS_CONV2D || pl.kind == MS_LINEAR || pl.kind == MS_CONV_TRANSPOSE2D || pl.kind == MS_CONV3D ||
+            pl.kind == MS_CONV_TRANSPOSE3D) && (pl.dtype == MS_F32 || pl.g.C % 8 != 0 || pl.g.K % 8 != 0);
+}
+
 size_t backward_workspace(const Plan &pl, uint32_t kernels) {
     size_t ws = 0;
     if (pl.kind == MS_CONV2D || pl.kind == MS_LINEAR) {
@@ -831,14 +837,14 @@ ms_status ms_layer_forward(const ms_layer *layer, const ms_tensor *x, const ms_t
     Plan lean;
     char *base = nullptr;
     if (sg.bytes + fb) {
-        int werr = -1;
+        int werr = has_lean(pl) ? -1 : 0;
         base = static_cast<char *>(ms::workspace_get(stream, sg.bytes + fb, &werr));
-        if (werr == 1 || werr == ms::kWsCapture) {
+        if ((werr == 1 || werr == ms::kWsCapture) && has_lean(pl)) {
             // the layer on the least it can do with
             lean = lean_plan(pl);
-            run = &lean;
             const size_t less = forward_workspace(lean);
             if (less < fb || werr == ms::kWsCapture) {
+                run = &lean;
                 fb = less;
                 werr = 0;
                 if (sg.bytes + fb) base = static_cast<char *>(ms::workspace_get(stream, sg.bytes + fb, &werr));
@@ -982,9 +988,9 @@ ms_status backward_impl(ms_record *r, const ms_tensor *grad_y, const ms_tensor *
                                                             "holds %zu", sg.bytes + kb, ms::kScratchBytes)
                                    : hip_fail(ms::device_last_error(), "scratch lookup");
     } else if (sg.bytes + kb) {
-        werr = -1;
+        werr = has_lean(full) ? -1 : 0;
         base = static_cast<char *>(ms::workspace_get(stream, sg.bytes + kb, &werr));
-        if ((werr == 1 || werr == ms::kWsCapture) && (go_lean() || werr == ms::kWsCapture)) {
+        if ((werr == 1 || werr == ms::kWsCapture) && has_lean(full) && (go_lean() || werr == ms::kWsCapture)) {
             werr = 0;
             if (sg.bytes + kb) base = static_cast<char *>(ms::workspace_get(stream, sg.bytes + kb, &werr));
         }

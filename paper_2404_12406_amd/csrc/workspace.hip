@@ -42,11 +42,9 @@ void *workspace_get(void *stream, size_t bytes, int *err) {
         *err = 2;
         return nullptr;
     }
-    std::lock_guard<std::mutex> lk(g_mu);
-    Buf &b = g_bufs[{dev, stream}];
-    if (b.n >= bytes) return b.p;
     if (optional) {
-        // allocating would end the capture
+        // a captured launch would keep the buffer's address, which the next
+        // growth frees; growing would end the capture
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing((hipStream_t)stream, &cs) != hipSuccess) {
             (void)hipGetLastError();
@@ -57,6 +55,9 @@ void *workspace_get(void *stream, size_t bytes, int *err) {
             return nullptr;
         }
     }
+    std::lock_guard<std::mutex> lk(g_mu);
+    Buf &b = g_bufs[{dev, stream}];
+    if (b.n >= bytes) return b.p;
     if (g_fail_next.load() > 0) {
         g_fail_next.fetch_sub(1);
         *err = 1;

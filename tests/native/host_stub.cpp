@@ -18,6 +18,7 @@ std::mutex g_mu;
 std::string g_log;
 std::string g_violation;
 int g_fail_next = 0;
+bool g_capturing = false;
 std::vector<void *> g_ws;
 struct Freer {
     ~Freer() {
@@ -48,6 +49,8 @@ void stub_reset() {
     g_log.clear();
     g_violation.clear();
 }
+// from now on, as if the stream were being captured
+void stub_capturing(int on) { g_capturing = on != 0; }
 // workspace growths (allocations) since the library was loaded
 long stub_workspace_allocations() {
     std::lock_guard<std::mutex> lk(g_mu);
@@ -57,11 +60,12 @@ long stub_workspace_allocations() {
 
 namespace ms {
 
-size_t conv_fwd_workspace(int, const ConvGeom &g) { return g.C % 8 ? 256 : 0; }
+// fp32 forwards and input gradients take partials unless they run lean
+size_t conv_fwd_workspace(int dtype, const ConvGeom &g) { return dtype == kF32 ? (g.lean ? 0 : 512) : g.C % 8 ? 256 : 0; }
 
-int launch_conv_fwd(int, const ConvGeom &g, const void *x, const void *w, const void *, void *y, void *ws, void *) {
-    log("conv_fwd");
-    if (g.C % 8 && (long long)g.N * g.P * g.Q * g.K > 0) need(ws, "conv_fwd:ws");
+int launch_conv_fwd(int dtype, const ConvGeom &g, const void *x, const void *w, const void *, void *y, void *ws, void *) {
+    log(g.lean ? "conv_fwd(lean)" : "conv_fwd");
+    if (conv_fwd_workspace(dtype, g) && (long long)g.N * g.P * g.Q * g.K > 0) need(ws, "conv_fwd:ws");
     const long long out = (long long)g.N * g.P * g.Q * g.K;
     const long long red = (long long)g.R * g.S * g.C;
     int e = 0;
@@ -71,14 +75,14 @@ int launch_conv_fwd(int, const ConvGeom &g, const void *x, const void *w, const 
 }
 
 size_t conv_dgrad_workspace(int dtype, const ConvGeom &g, bool) {
-    return dtype == kBF16 ? (size_t)g.K * g.R * g.S * g.C * 2 : 0;
+    return dtype == kBF16 ? (size_t)g.K * g.R * g.S * g.C * 2 : g.lean ? 0 : 512;
 }
 
 // never takes the bias gradient along: the runtime then launches the column sum
 int launch_conv_dgrad(int dtype, const ConvGeom &g, const void *dy, const void *w, const void *bias, void *dx,
                       void *ws, void *, void *, bool *db_done) {
     if (db_done) *db_done = false;
-    log(bias ? "conv_dgrad+bias" : "conv_dgrad");
+    log(g.lean ? "conv_dgrad(lean)" : bias ? "conv_dgrad+bias" : "conv_dgrad");
     if (conv_dgrad_workspace(dtype, g) > 0 && !ws) return need(false, "conv_dgrad:ws");
     const long long out = (long long)g.N * g.H * g.W * g.C;
     int e = 0;
@@ -196,8 +200,13 @@ int launch_avgpool_bwd(int, const void *dy, int N, int L, int C, void *dx, void 
 }
 
 void *workspace_get(void *, size_t bytes, int *err) {
+    const bool optional = *err < 0;
     *err = 0;
     if (bytes == 0) return nullptr;
+    if (optional && g_capturing) {
+        *err = kWsCapture;
+        return nullptr;
+    }
     std::lock_guard<std::mutex> lk(g_mu);
     if (g_fail_next > 0) {
         --g_fail_next;

@@ -14,6 +14,7 @@ import torch
 import oracle
 import paper_2404_12406_amd as ms
 import synth
+from paper_2404_12406_amd import _lib
 
 from _gpu import dev, guarded_empty, guards_intact, host
 
@@ -160,3 +161,41 @@ def test_f32_passes_captured_without_workspace():
         graph.replay()
         right(*got)
         right(*passes())
+
+
+@pytest.mark.parametrize("dtype,channels", [("f32", (128, 256)), ("bf16", (60, 100))])
+def test_captured_passes_hold_no_workspace(dtype, channels):
+    """An input gradient captured on a stream whose workspace would do: the graph
+    holds none of it (fp32 runs unsplit, ragged bf16 channels as with no room for
+    copies), so the stream may outgrow it and replays stay as they were."""
+    c, k = channels
+    xs, ws = (1, c, 4, 4), (k, c, 3, 3)
+    x, w = synth.normal(xs, 9710, dtype=dtype), synth.kaiming_uniform(ws, 9711, 9 * c, dtype=dtype)
+    X, W, G = (dev(t, dtype) for t in (x, w, synth.normal((1, k, 4, 4), 9712, dtype=dtype)))
+    lib = _lib.load()
+    recs = [ms.layer_forward(ms.Conv2d(1, 1), X, W, None, 1)[1] for _ in range(3)]
+    torch.cuda.synchronize()
+    with torch.cuda.stream(torch.cuda.Stream()):   # one that has no workspace yet
+        lib.ms_testing_fail_next_workspace(1)
+        without = ms.layer_backward(recs[0], G)[0]
+        lib.ms_testing_fail_next_workspace(0)
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        ms.layer_backward(recs[1], G)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        got = ms.layer_backward(recs[2], G)[0]
+    big, bw = (torch.randn(s, device="cuda", dtype=X.dtype) for s in ((2048, 4095), (1023, 4095)))
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        _, rec = ms.layer_forward(ms.Linear(), big, bw, None, 2)
+        ms.layer_backward(rec, torch.ones(2048, 1023, device="cuda", dtype=X.dtype))
+    torch.cuda.synchronize()
+    spare = [torch.full((1 << 19,), 3.0, device="cuda") for _ in range(8)]
+    for _ in range(3):
+        got.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got, without)
+        assert all(bool((t == 3.0).all()) for t in spare)

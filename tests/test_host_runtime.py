@@ -453,6 +453,55 @@ def test_workspace_failure_leaves_record_and_ledger_intact(stub):
     stub.ms_record_free(None)
 
 
+@pytest.mark.parametrize("why", ["capture", "failure"])
+def test_float_passes_without_a_workspace_run_lean(stub, why):
+    """An fp32 forward and input gradient under capture, or without memory for
+    their partials, run lean: they take no workspace and are not refused.  A
+    captured graph then holds no buffer that a later call may free."""
+    stub.stub_workspace_allocations.restype = ctypes.c_long
+    a = LayerArgs(wl.conv_sweep_bf16("10").layers[0], "f32")
+    stub.stub_reset()
+    logs = []
+    for lean in (False, True):
+        n0 = stub.stub_workspace_allocations()
+        h = ctypes.c_void_p()
+        gy, gx = tdesc(a.spec.out_shape(), "f32"), tdesc(tuple(a.x.shape[:4]), "f32")
+        try:
+            if lean and why == "capture":
+                stub.stub_capturing(1)
+            if lean and why == "failure":
+                stub.ms_testing_fail_next_workspace(1)
+            assert stub.ms_layer_forward(ctypes.byref(a.layer), ref(a.x), ref(a.W), ref(a.b), 1, ref(a.y), ctypes.byref(h), None) == 0
+            if lean and why == "failure":
+                stub.ms_testing_fail_next_workspace(1)
+            assert stub.ms_layer_backward(h, ref(gy), ref(gx), None, None, None) == 0
+        finally:
+            stub.stub_capturing(0)
+        stub.ms_record_free(h)
+        logs.append((stub.stub_log().decode(), stub.stub_workspace_allocations() - n0))
+        stub.stub_reset()
+    assert logs == [("conv_fwd;conv_dgrad;", 2), ("conv_fwd(lean);conv_dgrad(lean);", 0)]
+    assert stub.stub_violations().decode() == ""
+
+
+def test_capture_leaves_other_layers_their_workspace(stub):
+    """What has no lean form takes its workspace under capture as it did: a bf16
+    layer of whole vectors, an fp32 weight gradient."""
+    for dtype, mask, log in (("bf16", 1, "conv_fwd;conv_dgrad;"), ("f32", 2, "conv_fwd(lean);conv_wgrad;")):
+        a = LayerArgs(wl.conv_sweep_bf16("11").layers[0], dtype)
+        h = ctypes.c_void_p()
+        gy, gx, gw = (tdesc(tuple(s), dtype) for s in (a.spec.out_shape(), a.x.shape[:4], a.W.shape[:4]))
+        stub.stub_reset()
+        try:
+            stub.stub_capturing(1)
+            assert stub.ms_layer_forward(ctypes.byref(a.layer), ref(a.x), ref(a.W), ref(a.b), mask, ref(a.y), ctypes.byref(h), None) == 0
+            assert stub.ms_layer_backward(h, ref(gy), ref(gx) if mask & 1 else None, ref(gw) if mask & 2 else None, None, None) == 0
+        finally:
+            stub.stub_capturing(0)
+        stub.ms_record_free(h)
+        assert stub.stub_log().decode() == log and stub.stub_violations().decode() == ""
+
+
 def test_noalloc_backward_launches_the_same_plan_from_the_fixed_scratch(stub):
     """The no-allocation backward runs the launch plan of ms_layer_backward
     with its workspace taken from the fixed scratch (never the allocating
