@@ -1,7 +1,10 @@
 // Per-(device, stream) transient workspace for split-K partials and
 // reduction partials.  A buffer is reused by every call on its stream (the
 // stream orders those calls); it only grows, and growth first waits for the
-// stream so the old buffer is no longer in use.
+// stream so the old buffer is no longer in use.  A buffer whose address a graph
+// has captured is not freed when it is outgrown: the graph may still be replayed,
+// and nothing says when it is gone.  Such buffers stay until the process ends,
+// at most one for each growth that follows a capture.
 //
 // Also the fixed scratch array of the no-allocation backward: a file-scope
 // device array that every GPU the library runs on holds from the first
@@ -24,6 +27,7 @@ namespace {
 struct Buf {
     void *p = nullptr;
     size_t n = 0;
+    bool captured = false;   // a graph holds p
 };
 std::mutex g_mu;
 std::map<std::pair<int, void *>, Buf> g_bufs;
@@ -42,22 +46,22 @@ void *workspace_get(void *stream, size_t bytes, int *err) {
         *err = 2;
         return nullptr;
     }
-    if (optional) {
-        // a captured launch would keep the buffer's address, which the next
-        // growth frees; growing would end the capture
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing((hipStream_t)stream, &cs) != hipSuccess) {
-            (void)hipGetLastError();
-            cs = hipStreamCaptureStatusActive;
-        }
-        if (cs != hipStreamCaptureStatusNone) {
-            *err = kWsCapture;
-            return nullptr;
-        }
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing((hipStream_t)stream, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        cs = hipStreamCaptureStatusActive;
+    }
+    const bool capturing = cs != hipStreamCaptureStatusNone;
+    if (optional && capturing) {
+        *err = kWsCapture;
+        return nullptr;
     }
     std::lock_guard<std::mutex> lk(g_mu);
     Buf &b = g_bufs[{dev, stream}];
-    if (b.n >= bytes) return b.p;
+    if (b.n >= bytes) {
+        b.captured |= capturing;
+        return b.p;
+    }
     if (g_fail_next.load() > 0) {
         g_fail_next.fetch_sub(1);
         *err = 1;
@@ -68,9 +72,8 @@ void *workspace_get(void *stream, size_t bytes, int *err) {
             *err = 2;
             return nullptr;
         }
-        (void)hipFree(b.p);
-        b.p = nullptr;
-        b.n = 0;
+        if (!b.captured) (void)hipFree(b.p);
+        b = Buf{};
     }
     const size_t gran = size_t(2) << 20;
     const size_t want = (bytes + gran - 1) / gran * gran;
@@ -81,6 +84,7 @@ void *workspace_get(void *stream, size_t bytes, int *err) {
         return nullptr;
     }
     b.n = want;
+    b.captured = capturing;
     return b.p;
 }
 

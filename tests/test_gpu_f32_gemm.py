@@ -199,3 +199,29 @@ def test_captured_passes_hold_no_workspace(dtype, channels):
         torch.cuda.synchronize()
         assert torch.equal(got, without)
         assert all(bool((t == 3.0).all()) for t in spare)
+
+
+def test_outgrown_workspace_of_a_graph_is_kept():
+    """A bf16 forward on padded copies holds the stream's workspace in its graph:
+    a larger call on the stream does not free what replays write."""
+    x, w = synth.normal((2, 60, 9, 9), 9720, dtype="bf16"), synth.kaiming_uniform((64, 60, 3, 3), 9721, 540, dtype="bf16")
+    X, W = dev(x, "bf16"), dev(w, "bf16")
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        want, _ = ms.layer_forward(ms.Conv2d(1, 1), X, W, None, 0)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        got, _ = ms.layer_forward(ms.Conv2d(1, 1), X, W, None, 0)
+    big, bw = torch.randn(8192, 1023, device="cuda").bfloat16(), torch.randn(256, 1023, device="cuda").bfloat16()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        ms.layer_forward(ms.Linear(), big, bw, None, 0)
+    torch.cuda.synchronize()
+    spare = [torch.full((1 << 19,), 3.0, device="cuda") for _ in range(8)]
+    for _ in range(3):
+        got.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+        assert all(bool((t == 3.0).all()) for t in spare)
