@@ -47,7 +47,9 @@
  *    ms_last_error() gives a human-readable detail (thread-local).
  *  - Asynchronous device faults surface as MS_E_HIP from a later call.
  *  - Calls on different streams that overlap on one device are safe: each
- *    stream gets its own transient workspace.
+ *    stream gets its own transient workspace.  Calls from several threads on
+ *    one stream are too: a call that uses the workspace enqueues all of its
+ *    kernels before another takes it.
  */
 #ifndef MEMSAVE_H
 #define MEMSAVE_H

@@ -7,6 +7,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <mutex>
+
 namespace ms {
 
 enum Dtype : int { kF32 = 0, kBF16 = 1 };
@@ -148,9 +150,12 @@ int launch_copy4(int dtype, const void *src, const int64_t ext[4], const int64_t
 // *err on failure: 1 unavailable, 2 another HIP error.  With *err negative on
 // entry the caller can do with less: while the stream is being captured it gets
 // none, *err is kWsCapture, and the graph holds no buffer that a later call on
-// the stream may outgrow and free.
+// the stream may outgrow and free.  On success *hold owns the buffer: the caller
+// keeps it until its last kernel is enqueued, so that calls from several threads
+// on one stream do not mix their kernels over it.
 constexpr int kWsCapture = 3;
-void *workspace_get(void *stream, size_t bytes, int *err);
+using WorkspaceHold = std::unique_lock<std::mutex>;
+void *workspace_get(void *stream, size_t bytes, int *err, WorkspaceHold *hold);
 // Test hook: make the next `n` workspace growths fail.
 void workspace_fail_next(int n);
 

@@ -836,9 +836,10 @@ ms_status ms_layer_forward(const ms_layer *layer, const ms_tensor *x, const ms_t
     const Plan *run = &pl;
     Plan lean;
     char *base = nullptr;
+    ms::WorkspaceHold hold;   // until the last launch
     if (sg.bytes + fb) {
         int werr = has_lean(pl) ? -1 : 0;
-        base = static_cast<char *>(ms::workspace_get(stream, sg.bytes + fb, &werr));
+        base = static_cast<char *>(ms::workspace_get(stream, sg.bytes + fb, &werr, &hold));
         if ((werr == 1 || werr == ms::kWsCapture) && has_lean(pl)) {
             // the layer on the least it can do with
             lean = lean_plan(pl);
@@ -847,7 +848,7 @@ ms_status ms_layer_forward(const ms_layer *layer, const ms_tensor *x, const ms_t
                 run = &lean;
                 fb = less;
                 werr = 0;
-                if (sg.bytes + fb) base = static_cast<char *>(ms::workspace_get(stream, sg.bytes + fb, &werr));
+                if (sg.bytes + fb) base = static_cast<char *>(ms::workspace_get(stream, sg.bytes + fb, &werr, &hold));
             }
         }
         if (werr) return werr == 1 ? fail(MS_E_NOMEM, "workspace of %zu bytes unavailable", sg.bytes + fb)
@@ -980,6 +981,7 @@ ms_status backward_impl(ms_record *r, const ms_tensor *grad_y, const ms_tensor *
         return kb < was;
     };
     char *base = nullptr;
+    ms::WorkspaceHold hold;   // until the last launch
     int werr = 0;
     if (fixed_scratch) {
         if (sg.bytes + kb > ms::kScratchBytes) go_lean();
@@ -989,10 +991,10 @@ ms_status backward_impl(ms_record *r, const ms_tensor *grad_y, const ms_tensor *
                                    : hip_fail(ms::device_last_error(), "scratch lookup");
     } else if (sg.bytes + kb) {
         werr = has_lean(full) ? -1 : 0;
-        base = static_cast<char *>(ms::workspace_get(stream, sg.bytes + kb, &werr));
+        base = static_cast<char *>(ms::workspace_get(stream, sg.bytes + kb, &werr, &hold));
         if ((werr == 1 || werr == ms::kWsCapture) && has_lean(full) && (go_lean() || werr == ms::kWsCapture)) {
             werr = 0;
-            if (sg.bytes + kb) base = static_cast<char *>(ms::workspace_get(stream, sg.bytes + kb, &werr));
+            if (sg.bytes + kb) base = static_cast<char *>(ms::workspace_get(stream, sg.bytes + kb, &werr, &hold));
         }
         if (werr) return werr == 1 ? fail(MS_E_NOMEM, "workspace of %zu bytes unavailable", sg.bytes + kb)
                                    : hip_fail(ms::device_last_error(), "workspace");

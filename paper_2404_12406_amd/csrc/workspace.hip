@@ -28,8 +28,9 @@ struct Buf {
     void *p = nullptr;
     size_t n = 0;
     bool captured = false;   // a graph holds p
+    std::mutex mu;           // one call at a time, until its kernels are enqueued
 };
-std::mutex g_mu;
+std::mutex g_mu;   // the map; its buffers have their own
 std::map<std::pair<int, void *>, Buf> g_bufs;
 std::atomic<int> g_fail_next{0};
 }  // namespace
@@ -37,7 +38,7 @@ std::atomic<int> g_fail_next{0};
 void workspace_fail_next(int n) { g_fail_next.store(n); }
 
 // err: 0 ok, 1 allocation failed, 2 other HIP error
-void *workspace_get(void *stream, size_t bytes, int *err) {
+void *workspace_get(void *stream, size_t bytes, int *err, WorkspaceHold *hold) {
     const bool optional = *err < 0;
     *err = 0;
     if (bytes == 0) return nullptr;
@@ -56,10 +57,13 @@ void *workspace_get(void *stream, size_t bytes, int *err) {
         *err = kWsCapture;
         return nullptr;
     }
-    std::lock_guard<std::mutex> lk(g_mu);
+    g_mu.lock();
     Buf &b = g_bufs[{dev, stream}];
+    g_mu.unlock();
+    WorkspaceHold lk(b.mu);
     if (b.n >= bytes) {
         b.captured |= capturing;
+        *hold = std::move(lk);
         return b.p;
     }
     if (g_fail_next.load() > 0) {
@@ -73,7 +77,8 @@ void *workspace_get(void *stream, size_t bytes, int *err) {
             return nullptr;
         }
         if (!b.captured) (void)hipFree(b.p);
-        b = Buf{};
+        b.p = nullptr;
+        b.n = 0;
     }
     const size_t gran = size_t(2) << 20;
     const size_t want = (bytes + gran - 1) / gran * gran;
@@ -85,6 +90,7 @@ void *workspace_get(void *stream, size_t bytes, int *err) {
     }
     b.n = want;
     b.captured = capturing;
+    *hold = std::move(lk);
     return b.p;
 }
 

@@ -5,10 +5,13 @@
 // outputs is non-null and 16-byte-or-better plausible, logs the call, and
 // returns 0 -- or 77 when the host runtime handed a kernel a pointer it
 // must not use.  The workspace comes from host memory that nobody touches.
+#include <atomic>
+#include <chrono>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../paper_2404_12406_amd/csrc/device.h"
@@ -19,6 +22,9 @@ std::string g_log;
 std::string g_violation;
 int g_fail_next = 0;
 bool g_capturing = false;
+bool g_slow = false;
+std::mutex g_ws_mu;                    // the one stream's workspace
+std::atomic<std::thread::id> g_user;   // the thread that took it last
 std::vector<void *> g_ws;
 struct Freer {
     ~Freer() {
@@ -51,6 +57,8 @@ void stub_reset() {
 }
 // from now on, as if the stream were being captured
 void stub_capturing(int on) { g_capturing = on != 0; }
+// launches take their time and look whether their workspace is still theirs
+void stub_slow(int on) { g_slow = on != 0; }
 // workspace growths (allocations) since the library was loaded
 long stub_workspace_allocations() {
     std::lock_guard<std::mutex> lk(g_mu);
@@ -66,6 +74,10 @@ size_t conv_fwd_workspace(int dtype, const ConvGeom &g) { return dtype == kF32 ?
 int launch_conv_fwd(int dtype, const ConvGeom &g, const void *x, const void *w, const void *, void *y, void *ws, void *) {
     log(g.lean ? "conv_fwd(lean)" : "conv_fwd");
     if (conv_fwd_workspace(dtype, g) && (long long)g.N * g.P * g.Q * g.K > 0) need(ws, "conv_fwd:ws");
+    if (ws && g_slow) {
+        std::this_thread::sleep_for(std::chrono::milliseconds(1));
+        need(g_user == std::this_thread::get_id(), "conv_fwd:workspace of another call");
+    }
     const long long out = (long long)g.N * g.P * g.Q * g.K;
     const long long red = (long long)g.R * g.S * g.C;
     int e = 0;
@@ -199,7 +211,7 @@ int launch_avgpool_bwd(int, const void *dy, int N, int L, int C, void *dx, void 
     return (N > 0 && C > 0 && L > 0) ? need(dy && dx, "avgpool_bwd:dy,dx") : 0;
 }
 
-void *workspace_get(void *, size_t bytes, int *err) {
+void *workspace_get(void *, size_t bytes, int *err, WorkspaceHold *hold) {
     const bool optional = *err < 0;
     *err = 0;
     if (bytes == 0) return nullptr;
@@ -207,12 +219,16 @@ void *workspace_get(void *, size_t bytes, int *err) {
         *err = kWsCapture;
         return nullptr;
     }
-    std::lock_guard<std::mutex> lk(g_mu);
+    std::unique_lock<std::mutex> lk(g_mu);
     if (g_fail_next > 0) {
         --g_fail_next;
         *err = 1;
         return nullptr;
     }
+    lk.unlock();
+    *hold = WorkspaceHold(g_ws_mu);
+    lk.lock();
+    g_user = std::this_thread::get_id();
     void *p = std::malloc(bytes);
     g_ws.push_back(p);
     return p;

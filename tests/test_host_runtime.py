@@ -8,6 +8,7 @@ import ctypes
 import os
 import re
 import subprocess
+import threading
 
 import pytest
 
@@ -482,6 +483,27 @@ def test_float_passes_without_a_workspace_run_lean(stub, why):
         stub.stub_reset()
     assert logs == [("conv_fwd;conv_dgrad;", 2), ("conv_fwd(lean);conv_dgrad(lean);", 0)]
     assert stub.stub_violations().decode() == ""
+
+
+def test_threads_on_one_stream_do_not_share_a_workspace(stub):
+    """A call that took the stream's workspace has it until its last launch."""
+    def forwards():
+        a = LayerArgs(wl.conv_sweep_bf16("10").layers[0], "f32")
+        for _ in range(20):
+            h = ctypes.c_void_p()
+            stub.ms_layer_forward(ctypes.byref(a.layer), ref(a.x), ref(a.W), ref(a.b), 0, ref(a.y), ctypes.byref(h), None)
+
+    stub.stub_reset()
+    stub.stub_slow(1)
+    try:
+        threads = [threading.Thread(target=forwards) for _ in range(4)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+    finally:
+        stub.stub_slow(0)
+    assert stub.stub_violations().decode() == "" and stub.stub_log().decode().count("conv_fwd;") == 80
 
 
 def test_capture_leaves_other_layers_their_workspace(stub):
