@@ -31,11 +31,12 @@ int64_t ms_testing_live_records(void);
  * apply as they do to a launch. */
 int32_t ms_testing_gemm_plan(int32_t pass, const int32_t geom[13], int32_t out[10]);
 
-/* The fp32 planner's decision for the same geom and pass: out[4] = {splits of
+/* The fp32 planner's decision for the same geom and pass: out[5] = {splits of
  * the reduction (the few-channel weight gradient: its partial rows), bytes that
- * their partials take, blocks along grid z, bytes of workspace the runtime gives
- * the pass}.  Returns 0, or -1 for operands past 32-bit byte offsets. */
-int32_t ms_testing_float_plan(int32_t pass, const int32_t geom[13], int64_t out[4]);
+ * their partials take, blocks along grid z, whether the few-channel kernels take
+ * the pass (1) or the GEMM (0), bytes of workspace the runtime gives it}.
+ * Returns 0, or -1 for operands past 32-bit byte offsets. */
+int32_t ms_testing_float_plan(int32_t pass, const int32_t geom[13], int64_t out[5]);
 
 #ifdef __cplusplus
 }

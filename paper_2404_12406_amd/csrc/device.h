@@ -59,10 +59,11 @@ int launch_conv_dgrad(int dtype, const ConvGeom &g, const void *dy, const void *
 // the fast path does not take the contraction.
 int gemm_plan_info(int pass, const ConvGeom &g, int out[10]);
 
-// The same for fp32: out[0..3] = splits (of the few-channel weight gradient: its
-// partial rows), bytes that their partials take, blocks along grid z, bytes of
-// workspace that the pass is given.  -1 when the operands are past 32-bit offsets.
-int f32_plan_info(int pass, const ConvGeom &g, int64_t out[4]);
+// The same for fp32: out[0..4] = splits (of the few-channel weight gradient: its
+// partial rows), bytes that their partials take, blocks along grid z, whether the
+// few-channel kernels take the pass, bytes of workspace that it is given.  -1 when
+// the operands are past 32-bit offsets.
+int f32_plan_info(int pass, const ConvGeom &g, int64_t out[5]);
 
 // dw = weight gradient for grad dy and input x.  Needs conv_wgrad_workspace()
 // bytes of device workspace (may be 0).  When db is non-null the launcher may

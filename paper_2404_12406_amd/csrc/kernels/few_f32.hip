@@ -29,6 +29,7 @@
 //   3x3 16 -> 16, 32 x 128^2        63 /  72 / 113  ->  43 /  45 /  57
 //   7x7/2 3 -> 64, 16 x 224^2, dx        663        ->      127
 #include <algorithm>
+#include <cmath>
 
 #include "common.h"
 #include "lds_dma.h"
@@ -43,8 +44,20 @@ using g2::kOOB;
 constexpr int kPx = 4;               // output rows per lane
 constexpr int kBufBytes = 20 << 10;  // an input buffer at most
 constexpr int kCUs = 256;
-// lanes of a launch, and (row, 16-pixel strip) steps of a weight gradient, from which the kernels pay
-constexpr int64_t kMinUnits = 16384, kMinSteps = 4096;
+// Lanes of a launch, and pixels of a weight gradient, below which the GEMM is left
+// alone: it splits its reduction over CUs that these kernels leave idle.  3x3, us,
+// GEMM / here:
+//   lanes        8192         16384        32768        65536
+//   8 -> 8       7.4 / 8.6    9.8 / 9.0    14.8 / 9.6   25.4 / 11.1
+//   3 -> 16      7.8 / 8.5    10.0 / 9.4   15.5 / 11.3  25.2 / 15.2
+// (with three input channels or one tap they win by up to a third at any size).
+// Above it the estimates decide (fwd_us(), and the GEMM's est_us()).  The weight
+// gradient, with its sums' reduction:
+//   pixels       32768        65536        131072       262144
+//   4 -> 4       11.0 / 9.6   15.0 / 9.6   20.1 / 10.4  31.4 / 10.9
+//   8 -> 8       12.6 / 13.7  16.8 / 14.8  23.0 / 15.8  36.8 / 17.2
+//   16 -> 16     16.7 / 21.3  23.2 / 23.9  36.2 / 27.3  62.9 / 38.4
+constexpr int64_t kMinUnits = 16384, kMinPixels = 65536;
 
 struct Args {
     const float *in, *w, *bias;
@@ -462,6 +475,7 @@ bool al16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 // then as many strips of kPx rows as 256 lanes, the output and kBufBytes hold, fewer while the tiles would leave CUs without a block.
 struct Tiling {
     int cv, tw, rows;
+    double us;   // estimated time of the launch
     int64_t tiles, wfloats, bfloats;   // tiles of a phase (bound); floats of weights and of a buffer
     bool rt3;
     int64_t lds_bytes() const { return (wfloats + 2 * bfloats) * 4; }
@@ -489,9 +503,26 @@ bool tiling(const ConvGeom &g, Tiling *out) {
     while (t.rows > 1 && (int64_t)g.N * phases * tiles_w * ((strips + t.rows - 1) / t.rows) < kCUs) --t.rows;
     t.tiles = (int64_t)g.N * tiles_w * ((strips + t.rows - 1) / t.rows);
     t.bfloats = buf_bytes(t.rows) / 4;
-    if (buf_bytes(t.rows) > kBufBytes || t.lds_bytes() > 64 << 10 || t.tiles > INT32_MAX) return false;
-    // lanes with work: too few leave CUs idle that the GEMM's split reduction fills
+    if (buf_bytes(t.rows) > kBufBytes || t.lds_bytes() > 64 << 10 || t.tiles * 256 > UINT32_MAX) return false;
+    const int64_t pixels = (int64_t)g.N * oh * ow * phases;
     if ((int64_t)g.N * strips * ow * phases < kMinUnits) return false;
+    // The launch in us.  A tile takes its 4x4x1 products at 16 clocks each on
+    // every wave, whichever of its lanes have work (two thirds of that with tiles
+    // enough for several blocks a CU), or its loads: 16-byte pieces of pixels 4 C
+    // bytes apart, 700 a us and CU out of the caches, 260 where the input is past
+    // them and every chunk of channels fetches its lines again; pieces that share
+    // lines come cheaper.  Over a tile's chunks 0.3 us of latency each; over the
+    // launch, the bytes.  Over some 300 launches measured (1x1, 3x3 and 7x7, 2 to
+    // 256 channels, images of 1 to 224 pixels a side, both ways) the smaller of
+    // this estimate and the GEMM's names the faster kernel to within 10%, but for
+    // 1x1 on 14 x 14 with 16 channels (29 us here, 24 there).  A Linear, images of
+    // one pixel, is never it: 16384 x 768 -> 10 takes 4500 us here, 18 there.
+    const int cvn = cin / t.cv, kg = groups(cout);
+    const double rounds = (double)((t.tiles * phases + kCUs - 1) / kCUs);
+    const double products = tr * ts * (double)cin * kPx * kg * 16 / 2400 * (rounds > 3 ? 0.7 : 1.0);
+    const double bytes_in = 4.0 * g.N * (DG ? (double)g.P * g.Q : (double)g.H * g.W) * cin;
+    const double loads = (double)((t.rows * kPx - 1) * si + tr) * hc * cvn / (bytes_in > 96e6 ? 260 : 700) * std::min(1.0, cin / 16.0);
+    t.us = 4 + 0.3 * cvn + std::max(rounds * std::max(products, loads), (bytes_in + 4.0 * pixels * cout) / 4.5e6);
     *out = t;
     return true;
 }
@@ -545,19 +576,30 @@ int run(const ConvGeom &g, const void *in, const void *w, const void *bias, void
 
 }  // namespace
 
-// Whether the kernels take the forward / input gradient / weight gradient of
-// g (whose tensors the caller has found to fit 32-bit byte offsets).
-bool fwd_applies(const ConvGeom &g, const void *x) {
+// Estimated us of the forward / input gradient of g (whose tensors the caller has
+// found to fit 32-bit byte offsets); infinite where the kernels do not take it.
+double fwd_us(const ConvGeom &g, const void *x) {
     Tiling t;
-    return (g.C % 4 != 0 || al16(x)) && tiling<false>(g, &t);
+    return (g.C % 4 != 0 || al16(x)) && tiling<false>(g, &t) ? t.us : HUGE_VAL;
 }
-bool dgrad_applies(const ConvGeom &g, const void *dy) {
+double dgrad_us(const ConvGeom &g, const void *dy) {
     Tiling t;
-    return (g.K % 4 != 0 || al16(dy)) && tiling<true>(g, &t);
+    return (g.K % 4 != 0 || al16(dy)) && tiling<true>(g, &t) ? t.us : HUGE_VAL;
 }
+// Whether the kernel takes the weight gradient.  Lanes past a row's end work for
+// nothing, and the more the more groups of channels there are, so the share of a
+// strip's 16 columns that are pixels is bounded below.  About 400,000 pixels, us,
+// GEMM / here:
+//   image     4 x 4          7 x 7         10 x 10       14 x 14
+//   4 -> 4    42.9 / 30.8    42.5 / 19.0   42.6 / 15.4   42.3 / 12.2   (2 x 2: 29.4 / 45.6)
+//   8 -> 8    49.6 / 55.4    49.7 / 32.9   50.1 / 25.9   50.1 / 19.6
+//   16 -> 16  92.6 / 237     91.1 / 129    90.0 / 83.2   90.8 / 60.7
 bool wgrad_applies(const ConvGeom &g) {
-    return g.R == 3 && g.S == 3 && g.sh == 1 && g.sw == 1 && g.C >= 1 && g.C <= 16 && g.K >= 1 && g.K <= 16 &&
-           (int64_t)g.N * g.P * ((g.Q + 15) / 16) >= kMinSteps;
+    if (g.R != 3 || g.S != 3 || g.sh != 1 || g.sw != 1 || g.C < 1 || g.C > 16 || g.K < 1 || g.K > 16) return false;
+    const int blocks = (g.K > 8 ? 2 : 1) * (g.C > 8 ? 2 : 1);
+    const int groups = (g.K > 4 ? 2 : 1) * (g.C > 4 ? 2 : 1) * blocks;   // 1, 2, 4, 8 or 16
+    const double share = g.Q / (16.0 * ((g.Q + 15) / 16));
+    return share >= 0.2 + 0.1 * std::log2(groups) && (int64_t)g.N * g.P * g.Q >= kMinPixels * (groups > 4 ? 2 : 1);
 }
 
 int conv_fwd(const ConvGeom &g, const void *x, const void *w, const void *bias, void *y, hipStream_t st) {

@@ -37,6 +37,7 @@
 //   7x7/2 3 -> 64, 16 x 224^2 126 / 2068 / 202 ->   75 / 657 /  87
 //   512 x 768 x 768            73 /  87 /  22  ->   16 /  17 /  14
 #include <algorithm>
+#include <cmath>
 
 #include "common.h"
 #include "lds_dma.h"
@@ -47,8 +48,8 @@ namespace ms {
 
 // convolutions of few channels (few_f32.hip)
 namespace few {
-bool fwd_applies(const ConvGeom &g, const void *x);
-bool dgrad_applies(const ConvGeom &g, const void *dy);
+double fwd_us(const ConvGeom &g, const void *x);
+double dgrad_us(const ConvGeom &g, const void *dy);
 bool wgrad_applies(const ConvGeom &g);
 int conv_fwd(const ConvGeom &g, const void *x, const void *w, const void *bias, void *y, hipStream_t st);
 int conv_dgrad(const ConvGeom &g, const void *dy, const void *w, const void *bias, void *dx, hipStream_t st);
@@ -606,6 +607,7 @@ constexpr int64_t kPartialCap = int64_t(16) << 20;
 
 struct Plan {
     int tile, splits, k_split;
+    double us;   // estimated
 };
 
 // Estimated time of z GEMMs of M x N x K in us: the busiest CU's blocks, each
@@ -630,16 +632,15 @@ int64_t part_stride(int64_t elems) { return (elems + 3) / 4 * 4; }
 
 // `cap_bytes`: what the partials, part_stride(out_elems) apart, may take
 Plan plan(int mode, int64_t M, int64_t N, int64_t K, int z, int64_t out_elems, int64_t cap_bytes) {
-    Plan best{0, 1, 0};
-    double bt = 1e300;
+    Plan best{0, 1, 0, 1e300};
     for (int ti = 0; ti < kNumTiles; ++ti) {
         const TileInfo &t = kTiles[ti];
         if (t.bm == 32 && mode != kWgrad) continue;   // rows are pixels there: never few
         const int64_t most = std::max<int64_t>(1, std::min<int64_t>(K / (4 * BK), cap_bytes / std::max<int64_t>(1, 4 * part_stride(out_elems))));
         for (int64_t sp = 1; sp <= std::min<int64_t>(most, 1024); sp += sp < 16 ? 1 : sp / 8) {
             const double us = est_us(t, M, N, K, z, (int)sp);
-            if (us < bt * 0.999) {
-                bt = us;
+            if (us < best.us * 0.999) {
+                best.us = us;
                 best.tile = ti;
                 best.splits = (int)sp;
             }
@@ -773,8 +774,8 @@ int conv_fwd(const ConvGeom &g, const void *x, const void *w, const void *bias, 
     a.a = (const float *)x; a.b = (const float *)w; a.g = g;
     a.M = g.N * g.P * g.Q; a.N = g.K; a.K = g.R * g.S * g.C;
     if (a.M == 0 || a.N == 0) return 0;
-    if (few::fwd_applies(g, x)) return few::conv_fwd(g, x, w, bias, y, st);
     Plan p = fwd_plan(g);
+    if (few::fwd_us(g, x) < p.us) return few::conv_fwd(g, x, w, bias, y, st);
     if (p.splits > 1 && (!ws || !al16(ws))) p.splits = 1;
     return run<kFwd>(p, g.C % 4 == 0 && al16(x) && al16(w), a, 1, y_elems(g), (const float *)bias, (float *)y, ws, st);
 }
@@ -787,8 +788,8 @@ int conv_dgrad(const ConvGeom &g, const void *dy, const void *w, const void *bia
     a.M = g.N * Hb * Wb; a.N = g.C;
     a.K = ((g.R + g.sh - 1) / g.sh) * ((g.S + g.sw - 1) / g.sw) * g.K;
     if (a.M == 0 || a.N == 0) return 0;
-    if (few::dgrad_applies(g, dy)) return few::conv_dgrad(g, dy, w, bias, dx, st);
     Plan p = dgrad_plan(g);
+    if (few::dgrad_us(g, dy) < p.us) return few::conv_dgrad(g, dy, w, bias, dx, st);
     if (p.splits > 1 && (!ws || !al16(ws))) p.splits = 1;
     return run<kDgrad>(p, g.K % 4 == 0 && g.C % 4 == 0 && al16(dy) && al16(w), a, g.sh * g.sw, x_elems(g),
                        (const float *)bias, (float *)dx, ws, st);
@@ -812,23 +813,25 @@ int conv_wgrad(const ConvGeom &g, const void *dy, const void *x, void *dw, void 
 }
 
 // What a pass (0 forward, 1 input gradient, 2 weight gradient) lays out: out =
-// {splits, bytes of their partials, blocks along grid z}; -1: it is not taken.
-int plan_info(int pass, const ConvGeom &g, size_t cap, int64_t out[3]) {
+// {splits, bytes of their partials, blocks along grid z, whether the few-channel
+// kernels take it}; -1: it is not taken.
+int plan_info(int pass, const ConvGeom &g, size_t cap, int64_t out[4]) {
     if (!geom_ok(g)) return -1;
     const int z = pass == kDgrad ? g.sh * g.sw : 1;
     const int64_t elems = pass == kFwd ? y_elems(g) : pass == kDgrad ? x_elems(g) : w_elems(g);
-    const bool few = pass == kFwd ? few::fwd_applies(g, nullptr) : pass == kDgrad ? few::dgrad_applies(g, nullptr) : false;
-    const int rows = pass == kWgrad && elems > 0 ? few_rows(g, cap) : 0;
-    if (few || rows) {
-        out[0] = few ? 1 : rows;
-        out[1] = few ? 0 : rows * part_stride(elems) * 4;
-        out[2] = 1;
-        return 0;
-    }
     const Plan p = pass == kFwd ? fwd_plan(g) : pass == kDgrad ? dgrad_plan(g) : wgrad_plan(g, (int64_t)cap);
     out[0] = p.splits;
     out[1] = (int64_t)part_bytes(p, elems);
     out[2] = (int64_t)z * p.splits;
+    out[3] = 0;
+    const int rows = pass == kWgrad && elems > 0 ? few_rows(g, cap) : 0;
+    const double us = pass == kFwd ? few::fwd_us(g, nullptr) : pass == kDgrad ? few::dgrad_us(g, nullptr) : HUGE_VAL;
+    if (rows || us < p.us) {
+        out[0] = std::max(rows, 1);
+        out[1] = rows * part_stride(elems) * 4;
+        out[2] = z;
+        out[3] = 1;
+    }
     return 0;
 }
 

@@ -56,7 +56,7 @@ size_t dgrad_workspace(const ConvGeom &g);
 int conv_fwd(const ConvGeom &g, const void *x, const void *w, const void *bias, void *y, void *ws, hipStream_t st);
 int conv_dgrad(const ConvGeom &g, const void *dy, const void *w, const void *bias, void *dx, void *ws, hipStream_t st);
 int conv_wgrad(const ConvGeom &g, const void *dy, const void *x, void *dw, void *ws, size_t cap, hipStream_t st);
-int plan_info(int pass, const ConvGeom &g, size_t cap, int64_t out[3]);
+int plan_info(int pass, const ConvGeom &g, size_t cap, int64_t out[4]);
 }  // namespace f32g
 
 enum Mode { kFwd = 0, kDgrad = 1, kWgrad = 2 };
@@ -758,11 +758,11 @@ int launch_conv_wgrad(int dtype, const ConvGeom &g, const void *dy, const void *
     return (int)hipGetLastError();
 }
 
-int f32_plan_info(int pass, const ConvGeom &g, int64_t out[4]) {
-    out[3] = (int64_t)(pass == 0   ? conv_fwd_workspace(kF32, g)
+int f32_plan_info(int pass, const ConvGeom &g, int64_t out[5]) {
+    out[4] = (int64_t)(pass == 0   ? conv_fwd_workspace(kF32, g)
                        : pass == 1 ? conv_dgrad_workspace(kF32, g)
                                    : conv_wgrad_workspace(kF32, g, false));
-    return f32g::plan_info(pass, g, (size_t)out[3], out);
+    return f32g::plan_info(pass, g, (size_t)out[4], out);
 }
 
 }  // namespace ms

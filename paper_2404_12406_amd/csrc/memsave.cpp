@@ -1324,7 +1324,7 @@ int32_t ms_testing_gemm_plan(int32_t pass, const int32_t geom[13], int32_t out[1
     return r;
 }
 
-int32_t ms_testing_float_plan(int32_t pass, const int32_t geom[13], int64_t out[4]) {
+int32_t ms_testing_float_plan(int32_t pass, const int32_t geom[13], int64_t out[5]) {
     if (!geom || !out) return -1;
     const ms::ConvGeom g{geom[0], geom[1], geom[2], geom[3], geom[4], geom[5], geom[6],
                          geom[7], geom[8], geom[9], geom[10], geom[11], geom[12]};

@@ -266,8 +266,8 @@ int gemm_plan_info(int, const ConvGeom &, int out[10]) {
     return -1;
 }
 
-int f32_plan_info(int, const ConvGeom &, int64_t out[4]) {
-    for (int i = 0; i < 4; ++i) out[i] = 0;
+int f32_plan_info(int, const ConvGeom &, int64_t out[5]) {
+    for (int i = 0; i < 5; ++i) out[i] = 0;
     return -1;
 }
 

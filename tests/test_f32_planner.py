@@ -16,9 +16,9 @@ def lib():
 
 
 def plan(lib, pas, geom):
-    o = (ctypes.c_int64 * 4)()
+    o = (ctypes.c_int64 * 5)()
     assert lib.ms_testing_float_plan(pas, (ctypes.c_int32 * 13)(*geom), o) == 0, geom
-    return dict(zip(("splits", "partials", "z", "given"), o))
+    return dict(zip(("splits", "partials", "z", "few", "given"), o))
 
 
 def linear(m, k_in, n_out):
@@ -55,3 +55,35 @@ def test_partials_stay_inside_the_workspace(lib):
             assert p["partials"] <= p["given"], (pas, g, p)
             split += p["splits"] > 1
     assert split > 1000
+
+
+def square(c, k, s, n, f=3, stride=1):
+    return conv(n, c, s, s, k, f, f, (stride, stride), (f // 2, f // 2))
+
+
+# (pass, layer, whether the few-channel kernels were the faster ones by a fifth or more)
+FASTER = [
+    # a Linear is N images of one pixel: its tiles would hold one lane of 256
+    (FWD, linear(16384, 768, 10), 0), (FWD, linear(65536, 64, 1), 0), (FWD, linear(16384, 16, 16), 0),
+    (DGRAD, linear(16384, 16, 16), 0), (DGRAD, linear(1 << 25, 4, 4), 0), (FWD, linear(1 << 25, 4, 4), 0),
+    # small images leave lanes without a pixel, the more they cost the more groups of channels
+    (FWD, square(8, 8, 1, 60000), 0), (FWD, square(4, 4, 4, 25000), 0), (FWD, square(4, 4, 14, 2040), 1),
+    (DGRAD, square(2, 2, 10, 4000), 1), (FWD, square(8, 8, 10, 4000), 0), (FWD, square(8, 8, 20, 1000), 1),
+    (FWD, square(16, 16, 16, 1562), 0), (DGRAD, square(16, 16, 24, 694), 1),
+    # chunks of a few channels out of wide pixels fetch every line again
+    (FWD, square(64, 4, 56, 127, f=1), 0), (FWD, square(256, 4, 14, 2040, f=1), 0), (FWD, square(64, 16, 56, 24), 0),
+    (FWD, square(8, 8, 56, 127, f=1), 1), (FWD, square(64, 4, 64, 64), 1),
+    # few pixels
+    (FWD, square(16, 16, 64, 16), 0), (FWD, square(16, 16, 64, 128), 1), (FWD, square(8, 8, 64, 32), 1),
+    (DGRAD, square(3, 64, 224, 4, f=7, stride=2), 1), (DGRAD, square(3, 64, 32, 16, f=7, stride=2), 0),
+    (DGRAD, square(16, 32, 64, 16, stride=2), 0),
+    # the weight gradient
+    (WGRAD, square(4, 4, 2, 25000), 0), (WGRAD, square(4, 4, 4, 25000), 1), (WGRAD, square(8, 8, 4, 6250), 0),
+    (WGRAD, square(8, 8, 7, 8163), 1), (WGRAD, square(16, 16, 7, 8163), 0), (WGRAD, square(16, 16, 14, 2040), 1),
+    (WGRAD, square(16, 16, 64, 8), 0), (WGRAD, square(16, 16, 64, 32), 1), (WGRAD, square(8, 8, 256, 64), 1),
+]
+
+
+@pytest.mark.parametrize("pas,geom,few", FASTER)
+def test_few_channel_kernels_where_they_were_faster(lib, pas, geom, few):
+    assert plan(lib, pas, geom)["few"] == few

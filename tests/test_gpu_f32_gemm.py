@@ -53,6 +53,13 @@ CONVS = [
     ((5, 16, 131, 403), (16, 16, 3, 3), (1, 1), (2, 2)),     # sixteen both ways, wide padding
     ((3, 1, 301, 301), (2, 1, 5, 5), (1, 1), (2, 2)),        # one channel, 5 x 5
     ((16, 4, 257, 259), (24, 4, 7, 7), (2, 2), (3, 3)),      # strided phases of the input gradient
+    # few channels of one-pixel or small images: the GEMM's
+    ((16500, 36), (1, 36), None, None),
+    ((16500, 768), (10, 768), None, None),
+    ((20001, 12), (16, 12), None, None),
+    ((17000, 4, 1, 1), (5, 4, 3, 3), (1, 1), (1, 1)),
+    ((420, 16, 13, 13), (16, 16, 3, 3), (1, 1), (1, 1)),
+    ((33, 64, 56, 56), (4, 64, 1, 1), (1, 1), (0, 0)),
 ]
 
 
