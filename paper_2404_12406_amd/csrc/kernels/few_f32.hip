@@ -27,7 +27,7 @@
 // the GEMM tiles of gemm_f32.hip:
 //   3x3 8 -> 8, 64 x 256^2         310 / 375 / 428  ->  84 /  89 / 114
 //   3x3 16 -> 16, 32 x 128^2        63 /  72 / 113  ->  43 /  45 /  57
-//   7x7/2 3 -> 64, 16 x 224^2, dx        663        ->      127
+//   7x7/2 3 -> 64, 16 x 224^2, dx        663        ->      129
 #include <algorithm>
 #include <cmath>
 
@@ -42,6 +42,7 @@ namespace few {
 using g2::kOOB;
 
 constexpr int kPx = 4;               // output rows per lane
+constexpr int kFlush = 256;          // products an accumulator runs over
 constexpr int kBufBytes = 20 << 10;  // an input buffer at most
 constexpr int kCUs = 256;
 // Lanes of a launch, and pixels of a weight gradient, below which the GEMM is left
@@ -125,7 +126,13 @@ template <int CV> struct Vec { float e[CV]; };
 // LDS buffers, so one step's loads fly during the products of the step before.
 // A tile's stores have a fixed count and stay in flight past the next step's
 // wait.
-template <bool DG, int CV, int KG, int RT>
+//
+// LONG: sums of more than kFlush products.  An accumulator that has run over
+// kFlush of them is added to a second one and starts again, as in gemm_f32.hip: a
+// sum's rounding error grows with its longest chain (2304 equal products that a
+// large partial sum always rounds down: 3.4e-5 of the sum as one chain, at most
+// 8.4e-6 so).
+template <bool DG, int CV, int KG, int RT, bool LONG>
 __global__ __launch_bounds__(256) void conv_kernel(const Args P) {
     // weights [tap][c / CV][kg][4 output channels][4], the last index CV used;
     // then two input buffers [row][column][CV]
@@ -195,7 +202,7 @@ __global__ __launch_bounds__(256) void conv_kernel(const Args P) {
     // sent past the output
     const bool vec = (P.cout & 3) == 0 && (reinterpret_cast<uintptr_t>(P.out) & 15u) == 0;
 
-    floatx4 acc[kPx][KG];
+    floatx4 acc[kPx][KG], sum[LONG ? kPx : 1][LONG ? KG : 1];
     // the pixels' products of one tap, every accumulator once before any twice
     // (a chain on one accumulator waits for the result each time)
     auto fma = [&](const Vec<CV> *x, const floatx4 (&a)[KG]) __attribute__((always_inline)) {
@@ -212,13 +219,35 @@ __global__ __launch_bounds__(256) void conv_kernel(const Args P) {
         for (int k = 0; k < KG; ++k) a[k] = *reinterpret_cast<const floatx4 *>(wlane + ((tap * cvn + cv) * KG + k) * 16);
     };
 
+    // after a column of filter taps: products since the last flush
+    int run = 0;
+    const int column = v.tr * CV;
+    auto flush = [&]() __attribute__((always_inline)) {
+        if constexpr (LONG) {
+            run += column;
+            if (run + column <= kFlush) return;
+            run = 0;
+#pragma unroll
+            for (int px = 0; px < kPx; ++px)
+#pragma unroll
+                for (int k = 0; k < KG; ++k) {
+                    sum[px][k] += acc[px][k];
+                    acc[px][k] = floatx4{0.f, 0.f, 0.f, 0.f};
+                }
+        }
+    };
+
     int buf = 0, ltile = t0, lcv = 0;   // the step being loaded
     issue(0, t0, 0);
     for (int tile = t0; tile < t1; ++tile) {
 #pragma unroll
         for (int px = 0; px < kPx; ++px)
 #pragma unroll
-            for (int k = 0; k < KG; ++k) acc[px][k] = floatx4{0.f, 0.f, 0.f, 0.f};
+            for (int k = 0; k < KG; ++k) {
+                acc[px][k] = floatx4{0.f, 0.f, 0.f, 0.f};
+                if constexpr (LONG) sum[px][k] = acc[px][k];
+            }
+        run = 0;
         for (int cv = 0; cv < cvn; ++cv) {
             // this step's loads have landed (the stores of the tile before are
             // newer than they); the first wait covers the weights too
@@ -268,6 +297,7 @@ __global__ __launch_bounds__(256) void conv_kernel(const Args P) {
                         fma(in, a);
                     }
                 }
+                flush();
             }
         }
         const int tx = tile % tiles_w, t2 = tile / tiles_w, ty = t2 % tiles_h, n = t2 / tiles_h;
@@ -279,7 +309,9 @@ __global__ __launch_bounds__(256) void conv_kernel(const Args P) {
             const uint32_t off = (uint32_t)(((n * v.OH + v.h0 + (i0 + px) * v.sh) * v.OW + v.w0 + j * v.sw) * P.cout) * 4u;
 #pragma unroll
             for (int k = 0; k < KG; ++k) {
-                const floatx4 r = acc[px][k] + bias[k];
+                floatx4 r = acc[px][k];
+                if constexpr (LONG) r += sum[px][k];
+                r += bias[k];
                 u32x4 u;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) u[e] = __float_as_uint(r[e]);
@@ -475,7 +507,8 @@ bool al16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 // then as many strips of kPx rows as 256 lanes, the output and kBufBytes hold, fewer while the tiles would leave CUs without a block.
 struct Tiling {
     int cv, tw, rows;
-    double us;   // estimated time of the launch
+    double us;      // estimated time of the launch
+    int64_t products;   // of a sum, at most
     int64_t tiles, wfloats, bfloats;   // tiles of a phase (bound); floats of weights and of a buffer
     bool rt3;
     int64_t lds_bytes() const { return (wfloats + 2 * bfloats) * 4; }
@@ -492,6 +525,7 @@ bool tiling(const ConvGeom &g, Tiling *out) {
     const int si = DG ? 1 : g.sh, sj = DG ? 1 : g.sw, phases = DG ? g.sh * g.sw : 1;
     if (oh < 1 || ow < 1 || tr > 16 || ts > 16 || si > 4 || sj > 4 || phases > 65535) return false;
     t.rt3 = g.sh == 1 && g.R == 3;
+    t.products = (int64_t)tr * ts * cin;
     t.wfloats = ((int64_t)tr * ts * (cin / t.cv) * groups(cout) * 16 + 255) / 256 * 256;
     const int tiles_w = (ow + 63) / 64;
     t.tw = (ow + tiles_w - 1) / tiles_w;
@@ -530,9 +564,10 @@ bool tiling(const ConvGeom &g, Tiling *out) {
 template <bool DG, int CV, int KG>
 int go_rt(const Args &a, const Tiling &t, dim3 grid, hipStream_t st) {
     const unsigned pk = DG ? kProfDgrad : kProfFwd;
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), (size_t)t.lds_bytes(), st, a); };
     prof_mark(pk, st, true);
-    if (t.rt3) hipLaunchKernelGGL((conv_kernel<DG, CV, KG, 3>), grid, dim3(256), (size_t)t.lds_bytes(), st, a);
-    else hipLaunchKernelGGL((conv_kernel<DG, CV, KG, 0>), grid, dim3(256), (size_t)t.lds_bytes(), st, a);
+    if (t.rt3) t.products > kFlush ? go(conv_kernel<DG, CV, KG, 3, true>) : go(conv_kernel<DG, CV, KG, 3, false>);
+    else t.products > kFlush ? go(conv_kernel<DG, CV, KG, 0, true>) : go(conv_kernel<DG, CV, KG, 0, false>);
     const int err = (int)hipGetLastError();
     prof_mark(pk, st, false);
     return err;

@@ -6,7 +6,9 @@ tap mask holds, split and unsplit, strided phases with and without taps.
 Bar: with accumulators that run over at most 256 products and are then added
 up, every result is within (256 + K / 256 + 40) * 2^-24 of the sum of its
 products' magnitudes (K products; 40 bounds the split sums, the bias and the
-final rounding), which the oracle gives from the magnitudes of the operands."""
+final rounding), which the oracle gives from the magnitudes of the operands.
+Random operands stay far below it whatever the chains; equal products, of a size
+that the running sum rounds the same way each time, do not."""
 import numpy as np
 import pytest
 import torch
@@ -63,6 +65,17 @@ CONVS = [
 ]
 
 
+CHAINS = [
+    # result, images, channels, extent, filters, filter extent, stride
+    ("y", 16, 256, 64, 4, 3, 1),     # few channels out: chunks of four, 2304 products
+    ("y", 16, 64, 64, 4, 5, 1),      # 1600, any number of filter rows
+    ("y", 4, 3, 256, 2, 15, 1),      # 675, three channels at once
+    ("dx", 4, 3, 224, 64, 7, 2),     # 1024, the stride phases of an input gradient
+    ("y", 2, 256, 14, 64, 3, 1),     # the GEMM
+    ("dx", 2, 64, 14, 256, 3, 1),
+]
+
+
 @pytest.mark.parametrize("case", range(len(CONVS)))
 def test_f32_contractions(case):
     xs, ws, stride, pad = CONVS[case]
@@ -93,6 +106,33 @@ def test_f32_contractions(case):
     _within("y", host(y), ref, f(ax, aw, np.abs(b)), fan)
     _within("dx", host(gx), dx(gy, w), dx(ag, aw), ws[0] * fan // ws[1])
     _within("dW", host(gw), dw(gy, x), dw(ag, ax), pixels)
+
+
+@pytest.mark.parametrize("case", range(len(CHAINS)))
+def test_f32_long_sums_run_in_short_chains(case):
+    """Every product is p, whose low bits a partial sum of 2^e and more loses in
+    the same direction at each addition: a chain of K products is off by up to
+    K / 2 * 2^-24 of the sum, chains of 256 and their sum by at most (128 + K / 512
+    + 8) * 2^-24 (half of each bound, as the partial sums grow from zero)."""
+    pas, n, c, size, k, f, stride = CHAINS[case]
+    terms = f * f * c if pas == "y" else (-(-f // stride)) ** 2 * k
+    e = terms.bit_length() - (1 if terms >= 1.5 * 2 ** (terms.bit_length() - 1) else 2)
+    p = 1 + 2.0 ** (e - 24) - 2.0 ** -22
+    out = (size + 2 * (f // 2) - f) // stride + 1
+    w = torch.ones(k, c, f, f, device="cuda").contiguous(memory_format=torch.channels_last)
+    x = torch.full((n, c, size, size), p, device="cuda").contiguous(memory_format=torch.channels_last)
+    y, rec = ms.layer_forward(ms.Conv2d(stride, f // 2), x, w, None, 1)
+    if pas == "y":
+        ones = np.ones((1, 1, size, size))
+        count = c * oracle.conv2d_forward(ones, np.ones((1, 1, f, f)), None, (stride, stride), (f // 2, f // 2))
+        got = y
+    else:
+        ones = np.ones((1, 1, out, out))
+        count = k * oracle.conv2d_input_grad(ones, np.ones((1, 1, f, f)), (1, 1, size, size), (stride, stride), (f // 2, f // 2))
+        got = ms.layer_backward(rec, torch.full_like(y, p))[0]
+    assert count.max() == terms
+    err = np.abs(host(got) - p * count).max() / (p * terms)
+    assert err <= (128 + terms / 512 + 8) * 2.0 ** -24, err * 2.0 ** 24
 
 
 def test_f32_transposed_convolution_bias_and_output_padding():
