@@ -1650,14 +1650,15 @@ ConvGeom padded(const ConvGeom &g) {
 // Channels padded for a reduction over them and several taps: whole BK-deep
 // steps in one tap (tap-step loads) where that adds at most a quarter (32 x 28 x
 // 28, 96 -> 128 channels: the step's divisions cost 38%, the gradient through 96
-// 23.8 us, through 128 17.3).  Lean workspaces and one tap: multiples of 8.
-int pad_steps(const ConvGeom &g, int c) {
+// 23.8 us, through 128 17.3) and the padded operand of that many pixels still
+// fits.  Lean workspaces and one tap: multiples of 8.
+int pad_steps(const ConvGeom &g, int c, long pixels) {
     const int c8 = pad8(c), c64 = (c + BK - 1) / BK * BK;
-    return !g.lean && g.R * g.S > 1 && 4 * c64 <= 5 * c8 ? c64 : c8;
+    return !g.lean && g.R * g.S > 1 && 4 * c64 <= 5 * c8 && operand_fits(pixels * c64) ? c64 : c8;
 }
 ConvGeom padded_fwd(const ConvGeom &g) {
     ConvGeom q = g;
-    q.C = pad_steps(g, g.C);
+    q.C = pad_steps(g, g.C, (long)g.N * g.H * g.W);
     return q;
 }
 
@@ -2103,7 +2104,7 @@ int64_t colsum_rows(const ConvGeom &g, const Tile &t) {
 size_t pad_dy_bytes(const ConvGeom &g, int ldk) {
     return g.K % 8 == 0 ? 0 : al256((size_t)g.N * g.P * g.Q * ldk * sizeof(bf16));
 }
-int dgrad_ldk(const ConvGeom &g) { return g.K % 8 == 0 ? g.K : pad_steps(g, g.K); }
+int dgrad_ldk(const ConvGeom &g) { return g.K % 8 == 0 ? g.K : pad_steps(g, g.K, (long)g.N * g.P * g.Q); }
 // K padded (the pitch of the dy that the kernels read), and C (what the plans see)
 ConvGeom padded_k(const ConvGeom &g) {
     ConvGeom q = g;

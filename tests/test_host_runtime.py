@@ -160,6 +160,28 @@ def test_real_library_policy_without_gpu():
     assert lib.ms_version().decode().startswith("memsave")
 
 
+@pytest.mark.parametrize("images,channels", [(2000, 128), (2300, 104)])
+def test_padded_copies_stay_within_operand_offsets(images, channels):
+    """bf16 convolutions of 97 channels run on copies padded to 128, a whole step of
+    the reduction, while such a copy stays below 2^31 elements, else to 104: the
+    input gradients of a transposed convolution (its forward contraction) and of a
+    convolution, as their workspace shows."""
+    if not os.path.exists(L.LIB_PATH):
+        pytest.skip("libmemsave.so not built")
+    lib = L.load()
+    px = 90 * 90
+    assert px * images * channels < 2 ** 31 and (channels == 128 or px * images * 128 > 2 ** 31)
+    x = tdesc((images, 8, 90, 90))
+    for kind, W in ((L.MS_CONV_TRANSPOSE2D, tdesc((8, 97, 3, 3))), (L.MS_CONV2D, tdesc((97, 8, 3, 3)))):
+        layer = L.MsLayer()
+        layer.kind = kind
+        layer.stride[0] = layer.stride[1] = layer.pad[0] = layer.pad[1] = 1
+        acct = L.MsAccount()
+        assert lib.ms_policy_account(ctypes.byref(layer), ref(x), ref(W), None, 1, 0, ctypes.byref(acct)) == 0
+        copy = px * images * channels * 2
+        assert copy <= acct.transient_workspace_bytes < copy * 1.1, (kind, acct.transient_workspace_bytes / (px * images * 2))
+
+
 # ------------------------------------------------------------------ save rule
 @pytest.mark.parametrize("label,spec,dtype", ALL_LAYERS, ids=[a[0] for a in ALL_LAYERS])
 def test_policy_account_matches_closed_form(stub, label, spec, dtype):
