@@ -198,22 +198,21 @@ _MAX_DESCS = 256
 
 
 def _layer_desc(spec):
-    """_LayerDesc(spec); that of a Conv2d (its stride and pad numbers or tuples)
-    or a ReLU is built once per value."""
+    """_LayerDesc(spec); that of a Conv2d (its stride and pad integers or tuples of
+    them) or a ReLU is built once per value."""
     t = type(spec)
     if t is Conv2d:
         s, p = spec.stride, spec.pad
-        if type(s) not in (int, tuple) or type(p) not in (int, tuple):
-            return _LayerDesc(spec)
+        for v in (s, p):
+            # (other numbers may hash by identity and change their value)
+            if type(v) is not int and (type(v) is not tuple or any(type(e) is not int for e in v)):
+                return _LayerDesc(spec)
         key = (s, p)
     elif t is ReLU:
         key = ReLU
     else:
         return _LayerDesc(spec)
-    try:
-        d = _DESCS.get(key)
-    except TypeError:   # a tuple of what cannot be a key
-        return _LayerDesc(spec)
+    d = _DESCS.get(key)
     if d is None:
         d = _LayerDesc(spec)
         if len(_DESCS) < _MAX_DESCS:

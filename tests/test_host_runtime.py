@@ -160,6 +160,19 @@ def test_real_library_policy_without_gpu():
     assert lib.ms_version().decode().startswith("memsave")
 
 
+def test_layer_descriptors_are_kept_by_value_only():
+    """A stride that can change in place is read each time."""
+    import torch
+    from paper_2404_12406_amd import api
+    step = torch.tensor(1)
+    spec = api.Conv2d((step, step), 1)
+    assert api._layer_desc(spec).layer.stride[0] == 1
+    step.fill_(2)
+    assert api._layer_desc(spec).layer.stride[0] == 2
+    assert api._layer_desc(api.Conv2d((2, 1), 1)) is api._layer_desc(api.Conv2d((2, 1), 1))
+    assert api._layer_desc(api.Conv2d([2, 1], 1)).layer.stride[1] == 1
+
+
 @pytest.mark.parametrize("images,channels", [(2000, 128), (2300, 104)])
 def test_padded_copies_stay_within_operand_offsets(images, channels):
     """bf16 convolutions of 97 channels run on copies padded to 128, a whole step of
