@@ -9,6 +9,8 @@ products' magnitudes (K products; 40 bounds the split sums, the bias and the
 final rounding), which the oracle gives from the magnitudes of the operands.
 Random operands stay far below it whatever the chains; equal products, of a size
 that the running sum rounds the same way each time, do not."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -142,6 +144,25 @@ def test_f32_transposed_convolution_bias_and_output_padding():
     ref = oracle.convt2d_forward(x, w, b, stride, pad, op)
     y, _ = ms.layer_forward(ms.ConvTranspose2d(stride, pad, op), dev(x, "f32"), dev(w, "f32"), dev(b, "f32"), 0)
     _within("y", host(y), ref, oracle.convt2d_forward(np.abs(x), np.abs(w), np.abs(b), stride, pad, op), 32 * 12)
+
+
+@pytest.mark.parametrize("xs,ws,stride,op", [
+    ((16, 8, 101, 150), (8, 8, 3, 3), (1, 1), (0, 0)),    # whole output vectors
+    ((6, 12, 99, 81), (12, 5, 4, 3), (2, 2), (1, 0)),     # strided phases, five output channels
+])
+def test_f32_few_channel_transposed_forward_with_bias(xs, ws, stride, op):
+    """The few-channel input-gradient kernel with a bias: a transposed forward."""
+    pad = (1, 1)
+    x, w = synth.normal(xs, 9510, dtype="f32"), synth.kaiming_uniform(ws, 9511, ws[0] * ws[2] * ws[3], dtype="f32")
+    b = synth.normal((ws[1],), 9512, 1.0, dtype="f32")
+    ref = oracle.convt2d_forward(x, w, b, stride, pad, op)
+    geom = (xs[0], ws[1], *ref.shape[2:], ws[0], *ws[2:], *xs[2:], *stride, *pad)
+    plan = (C.c_int64 * 5)()
+    assert _lib.load().ms_testing_float_plan(1, (C.c_int32 * 13)(*geom), plan) == 0 and plan[3] == 1
+    out, buf, guard = guarded_empty(ref.shape, "f32")
+    y, _ = ms.layer_forward(ms.ConvTranspose2d(stride, pad, op), dev(x, "f32"), dev(w, "f32"), dev(b, "f32"), 0, y=out)
+    assert guards_intact(buf, guard)
+    _within("y", host(y), ref, oracle.convt2d_forward(np.abs(x), np.abs(w), np.abs(b), stride, pad, op), ws[0] * ws[2] * ws[3])
 
 
 @pytest.mark.parametrize("channels", [32, 6])
