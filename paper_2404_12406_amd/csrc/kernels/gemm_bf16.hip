@@ -760,6 +760,8 @@ int transpose_krsc(const void *w, bf16 *wt, int K, int RS, int C, hipStream_t st
     return (int)hipGetLastError();
 }
 
+constexpr long kGridYZ = 65535;   // blocks of a launch along y and z
+
 // The same for channel counts that are not multiples of 8: Wt[c][rs][k] =
 // W[k][rs][c], zero for k >= K or c >= C, of rows c < Cr and ldk k's each.  32 x
 // 32 tiles through LDS (small: a filter of a few ten thousand elements has to
@@ -2116,9 +2118,11 @@ bool ragged(const ConvGeom &g) { return g.K % 8 != 0 || g.C % 8 != 0; }
 // in each gradient, and the 2-byte loads of igemm.hip cost more at every size
 // tried.  (16, 60, 57, 45), 100 filters of 3x3, step 2, us with every pass: input
 // gradient 62 there, 25 here; weight and bias gradients 68 there, 29 here.
+// The filter's transpose has its taps along grid z and its k along grid y.
 bool pad_dy_fits(const ConvGeom &g) {
     const long ldk = dgrad_ldk(g);
-    return operand_fits((long)g.N * g.P * g.Q * ldk) && operand_fits(ldk * g.R * g.S * pad8(g.C));
+    return operand_fits((long)g.N * g.P * g.Q * ldk) && operand_fits(ldk * g.R * g.S * pad8(g.C)) &&
+           (long)g.R * g.S <= kGridYZ && (ldk + 31) / 32 <= kGridYZ;
 }
 
 // transposed filter (when used), then split-K partials indexed by dx pixel,
@@ -2512,7 +2516,7 @@ bool fwd3_ok(const Conv3dGeom &q) { return q.C % BK == 0 && q.g.K % 8 == 0 && q.
 bool dgrad3_ok(const Conv3dGeom &q) {
     const ConvGeom &g = q.g;
     return q.sd == 1 && g.K % BK == 0 && q.C % 8 == 0 &&
-           q.T * ((g.R + g.sh - 1) / g.sh) * ((g.S + g.sw - 1) / g.sw) <= 32 && fits3(q);
+           q.T * ((g.R + g.sh - 1) / g.sh) * ((g.S + g.sw - 1) / g.sw) <= 32 && (long)q.T * g.R * g.S <= kGridYZ && fits3(q);
 }
 bool wgrad3_ok(const Conv3dGeom &q) { return q.C % 8 == 0 && q.g.K % 8 == 0 && fits3(q); }
 

@@ -195,6 +195,22 @@ def test_padded_copies_stay_within_operand_offsets(images, channels):
         assert copy <= acct.transient_workspace_bytes < copy * 1.1, (kind, acct.transient_workspace_bytes / (px * images * 2))
 
 
+@pytest.mark.parametrize("filters,channels,taps,padded", [(5, 8, (255, 257), 1), (5, 8, (256, 257), 0), (2097113, 8, (1, 1), 1),
+                                                          (2097129, 8, (1, 1), 0)])
+def test_padded_gradients_stay_within_the_launch_limits(filters, channels, taps, padded):
+    """The transposed filter of a ragged bf16 gradient takes a block a tap and one
+    for each 32 filters, 65535 at most of either; past them no copy is planned."""
+    if not os.path.exists(L.LIB_PATH):
+        pytest.skip("libmemsave.so not built")
+    layer = L.MsLayer()
+    layer.kind = L.MS_CONV2D
+    layer.stride[0] = layer.stride[1] = 1
+    acct = L.MsAccount()
+    x, w = tdesc((2, channels, *taps)), tdesc((filters, channels, *taps))
+    assert L.load().ms_policy_account(ctypes.byref(layer), ref(x), ref(w), None, 1, 0, ctypes.byref(acct)) == 0
+    assert (acct.transient_workspace_bytes > 0) == padded
+
+
 # ------------------------------------------------------------------ save rule
 @pytest.mark.parametrize("label,spec,dtype", ALL_LAYERS, ids=[a[0] for a in ALL_LAYERS])
 def test_policy_account_matches_closed_form(stub, label, spec, dtype):
