@@ -12,8 +12,8 @@ gradients: 96 GEMMs, no weight-gradient GEMM (the mask skips it), through the
 C ABI of libmemsave.so.  `value` is the algorithmic TFLOP/s of the launched
 contractions over K back-to-back steps with every input resident in HBM.
 
-The same line carries, for the headline and for every other synthetic
-workload:
+The line carries for the headline, and a record on stderr for every other
+synthetic workload:
   * the timing protocol: K reps, each after a 512 MiB read sweep that evicts
     the last-level cache, as median / p10 / p90, next to the warm
     back-to-back figure;
@@ -28,7 +28,8 @@ and the roofline of the headline's dominant kernel, the HBM bytes the
 hardware counters recorded for it, and the CPU oracle timed on a bounded
 sample of the headline workload (plus a sampled oracle time per workload).
 
-One JSON line goes to stdout; progress goes to stderr.
+One JSON line goes to stdout; progress and the other workloads' records go to
+stderr.
 """
 from __future__ import annotations
 
@@ -1042,6 +1043,19 @@ def workload_by_name(name):
     return table[name]()
 
 
+DETAIL_KEYS = ("extra", "oracle_samples")
+
+
+def emit(line):
+    """The result on stdout as one line of a few KB; the other workloads'
+    records, 30 KB and more, on stderr: a reader that keeps the last 16 KB of
+    stdout lost the line's start to them."""
+    detail = {k: line[k] for k in DETAIL_KEYS if k in line}
+    if detail:
+        log("[bench] detail " + json.dumps(detail))
+    print(json.dumps({k: v for k, v in line.items() if k not in detail}), flush=True)
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -1129,7 +1143,7 @@ def main():
         log(f"[bench] cpu baseline {line['cpu_baseline']}")
         line["oracle_samples"] = oracle_samples()
         log(f"[bench] oracle samples {line['oracle_samples']}")
-    print(json.dumps(line), flush=True)
+    emit(line)
 
 
 if __name__ == "__main__":
