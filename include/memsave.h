@@ -162,7 +162,7 @@ enum { MS_K_DGRAD = 1u, MS_K_WGRAD = 2u, MS_K_BGRAD = 4u };
 typedef struct {
     uint64_t saved_activation_bytes;  /* bytes of non-parameter tensors kept (the layer input) */
     uint64_t referenced_param_bytes;  /* bytes of parameters / running stats kept by reference */
-    uint64_t transient_workspace_bytes; /* workspace the backward needs (released after it)   */
+    uint64_t transient_workspace_bytes; /* workspace the backward asks for (released after it) */
     uint32_t mask;                    /* the mask the record was created with               */
     uint32_t borrowed;                /* MS_SAVED_* bits                                   */
     uint32_t kernels;                 /* MS_K_* bits: backward launch plan                  */
@@ -192,7 +192,9 @@ enum {
  * y is caller-allocated and fully overwritten.  A bf16 convolution whose
  * channel count is not a multiple of 8 uses transient workspace for
  * zero-padded channel copies (MS_E_NOMEM if it cannot be had; nothing is
- * launched then).
+ * launched then).  An fp32 contraction may split its reduction over transient
+ * workspace; where that cannot be had, and while the stream is being captured,
+ * it runs unsplit (other bits of the same sums).
  */
 ms_status ms_layer_forward(const ms_layer *layer, const ms_tensor *x, const ms_tensor *W,
                            const ms_tensor *b, uint32_t mask, const ms_tensor *y,
@@ -286,8 +288,10 @@ ms_status ms_layer_backward(ms_record *rec, const ms_tensor *grad_y, const ms_te
  * call allocates nothing (no hipMalloc, hipFree or allocating library
  * routine) and records no profiling events.
  * A backward whose workspace (ms_account.transient_workspace_bytes of the
- * record) exceeds the scratch returns MS_E_UNSUPPORTED before anything is
- * launched; the record is then not consumed and may go to
+ * record) exceeds the scratch runs on the least it can do with (fp32 input
+ * gradients unsplit, ragged bf16 channels without padded copies); where that
+ * exceeds the scratch too it returns MS_E_UNSUPPORTED before anything is
+ * launched, and the record is then not consumed and may go to
  * ms_layer_backward() instead.
  * Every call on one GPU uses the same scratch bytes, which keep the last
  * call's contents (no kernel reads scratch it has not written in the same

@@ -27,7 +27,12 @@
 // 3x3x3, us a pass with all its kernels, folded -> not: forward 216 -> 170, input
 // gradient 240 -> 155, weight gradient 243 -> 195; and the input gradient rounds
 // once (error 2.4e-3 -> 1.7e-3).  Their workspace stays the folded form's, which
-// tensors off 16-byte alignment take.
+// tensors off 16-byte alignment take: it is asked for before a tensor's address is
+// looked at.
+//
+// fp32 layers fold.  Their forward and input gradient get no workspace beyond the
+// fold's, so that no call asks for more than the folded form needs, and run
+// unsplit; small ones leave CUs idle for it.
 #include <algorithm>
 
 #include "common.h"

@@ -23,9 +23,9 @@
 // core (timed without loads: 75 us for 9216 a SIMD), so 8 x 8 channels are bound
 // by it (62 us) next to HBM (54 us at the rate of a large copy).
 //
-// Measured, us (kernel; forward / input gradient / weight gradient), against
-// the GEMM tiles of gemm_f32.hip:
-//   3x3 8 -> 8, 64 x 256^2         310 / 375 / 428  ->  84 /  89 / 114
+// Measured, us (kernel, warm; forward / input gradient / weight gradient),
+// against the GEMM tiles of gemm_f32.hip:
+//   3x3 8 -> 8, 64 x 256^2         310 / 375 / 428  ->  79 /  83 / 103
 //   3x3 16 -> 16, 32 x 128^2        63 /  72 / 113  ->  43 /  45 /  57
 //   7x7/2 3 -> 64, 16 x 224^2, dx        663        ->      129
 #include <algorithm>

@@ -30,12 +30,13 @@
 // Tile and split of the reduction are chosen by plan() below.
 //
 // Measured against the 16x16x4 kernel of igemm.hip that it replaces (us a
-// contraction, forward / input gradient / weight gradient, warm):
-//   4096 x 1024 x 4096        320 / 457 / 424  ->  258 / 261 / 258 (133 TFLOP/s)
-//   3x3 64 -> 64, 32 x 56^2   191 / 215 / 275  ->   84 /  86 /  87
-//   3x3 256 -> 256, 32 x 14^2 218 / 300 / 120  ->   85 /  88 /  72
-//   7x7/2 3 -> 64, 16 x 224^2 126 / 2068 / 202 ->   75 / 657 /  87
-//   512 x 768 x 768            73 /  87 /  22  ->   16 /  17 /  14
+// contraction, forward / input gradient / weight gradient, warm: after some 30
+// passes; the first dozen after idling run at a lower clock, 10 to 17% slower):
+//   4096 x 1024 x 4096        320 / 457 / 424  ->  260 / 265 / 267 (130 TFLOP/s)
+//   3x3 64 -> 64, 32 x 56^2   191 / 215 / 275  ->   76 /  79 /  79
+//   3x3 256 -> 256, 32 x 14^2 218 / 300 / 120  ->   85 /  88 /  78
+//   7x7/2 3 -> 64, 16 x 224^2 126 / 2068 / 202 ->   75 / 664 /  87
+//   512 x 768 x 768            73 /  87 /  22  ->   20 /  20 /  18
 #include <algorithm>
 #include <cmath>
 
@@ -70,7 +71,9 @@ constexpr int BK = 32;    // reduction step: a 128-byte row
 // more before, and its error is to be no larger.
 template <int MODE> constexpr int flush_steps() { return MODE == kWgrad ? 4 : 8; }
 
-// Division of n < 2^31 by a fixed d >= 1: q = (umulhi(n, m) + n) >> s.
+// Division of n < 2^31 by a fixed d >= 1: q = (umulhi(n, m) + n) >> s, the
+// round-up reciprocal of Granlund and Montgomery, Division by Invariant Integers
+// using Multiplication (1994).
 struct FastDiv {
     uint32_t m, s, d;
 };
@@ -412,7 +415,8 @@ __global__ __launch_bounds__(256, OCC) void gemm_kernel(const Args P) {
 
     // acc runs over kFlush steps, then is added to sum: the rounding errors of
     // a K-long sum grow like sqrt(256 + K / 256) instead of sqrt(K).  Against 64
-    // bits, 4096 x 1024 x 4096: 1.1e-6 as one chain, 3.0e-7 so.
+    // bits, forward, input and weight gradient of 4096 x 1024 x 4096: 2.9e-7,
+    // 3.0e-7 and 2.3e-7; the three together 5.7e-7 as one chain, 2.9e-7 so.
     constexpr int kFlush = flush_steps<MODE>();
     floatx16 acc[TM][TN], sum[TM][TN];
 #pragma unroll
@@ -598,7 +602,21 @@ struct TileInfo {
     double eff;   // share of the fp32 MFMA rate when CUs are full
 };
 // 128 x 128 first; 32-wide columns for few output channels, 32-wide rows
-// for a weight gradient of few
+// for a weight gradient of few.  The shares, and est_us() with its splits, against
+// measurement (us measured / estimated, every tile forced; * the planner's choice):
+//                                128x128     128x64      64x64       128x32      32x128
+//   512 x 768 x 768, forward     24.4/22.7  *19.3/17.8   17.6/18.3   18.3/18.7
+//   2048 x 1024 x 1024, dx       51.8/51.8  *45.0/41.8   40.9/45.0   44.5/47.8
+//   3x3 64 -> 64, 32 x 56^2       174/169    92.7/92.4  *80.7/89.5   87.6/95.1
+//     weight gradient             152/140     150/135   *82.6/82.6    140/156     104/89.7
+//   3x3 256 -> 256, 32 x 14^2    86.5/91.0  *85.9/83.9   78.6/91.2   83.5/97.2
+//     weight gradient           *77.5/76.4   74.3/78.6   81.7/84.3   74.2/89.2   90.6/89.2
+//   3x3 512 -> 512, 32 x 7^2     84.0/91.0   89.2/89.5  *70.6/84.1   88.3/103
+//   3x3 32 -> 32, 16 x 64^2      50.7/47.7   29.8/27.9   28.4/29.9  *19.6/19.1
+//     weight gradient            69.4/63.4   58.2/53.1   35.0/34.8   53.0/58.7  *29.1/27.7
+// Over 30 such passes the choice is within 5% of the fastest tile, but for five
+// where 64 x 64, whose share is 10% low on whole reduction steps, was 6 to 13%
+// faster.
 constexpr TileInfo kTiles[] = {{128, 128, 2, 0.85}, {128, 64, 3, 0.82}, {64, 64, 4, 0.75}, {128, 32, 4, 0.70}, {32, 128, 4, 0.70}};
 constexpr int kNumTiles = 5;
 constexpr int kCUs = 256;

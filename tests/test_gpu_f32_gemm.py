@@ -3,10 +3,11 @@ rows and columns of every tile, channel counts with and without whole
 vectors, reductions of whole steps in one tap and not, more taps than a
 tap mask holds, split and unsplit, strided phases with and without taps.
 
-Bar: with accumulators that run over at most 256 products and are then added
-up, every result is within (256 + K / 256 + 40) * 2^-24 of the sum of its
-products' magnitudes (K products; 40 bounds the split sums, the bias and the
-final rounding), which the oracle gives from the magnitudes of the operands.
+Bar: with accumulators that run over at most 256 products (the few-channel weight
+gradient's over at most K / 4096, if that is more) and are then added up, every
+result is within (256 + K / 256 + 40) * 2^-24 of the sum of its products'
+magnitudes (K products; 40 bounds the split sums, the bias and the final
+rounding), which the oracle gives from the magnitudes of the operands.
 Random operands stay far below it whatever the chains; equal products, of a size
 that the running sum rounds the same way each time, do not."""
 import ctypes as C
