@@ -15,6 +15,8 @@ And on their instructions:
 
 * a load into LDS never follows a write of M0 directly: the hardware needs one
   wait state between them, which the compiler does not add in inline assembly;
+* nor does a vector-memory instruction read a scalar register that a vector
+  instruction wrote less than five wait states before, for the same reason;
 * the step barrier of the fp32 GEMM waits for the wave's own LDS reads: the loads
   that refill the stage behind it are in inline assembly, so the compiler does
   not order them after those reads.
@@ -147,6 +149,31 @@ def test_loads_into_lds_keep_their_distance_from_m0(listings):
                 if re.match(r"s_\w+ m0,", before):
                     bad.append((name, ins))
     assert loads > 1000 and not bad, (loads, len(bad), bad[:3])
+
+
+def _scalars(operands):
+    regs = set(re.findall(r"(?<![\w\[:])s(\d+)\b", operands))
+    for lo, hi in re.findall(r"\bs\[(\d+):(\d+)\]", operands):
+        regs |= {str(r) for r in range(int(lo), int(hi) + 1)}
+    return regs
+
+
+def test_memory_instructions_keep_their_distance_from_scalars_of_vector_writes(listings):
+    reads, bad = 0, []
+    for name, body in listings.items():
+        for i, ins in enumerate(body):
+            if not ins.startswith(("buffer_", "global_")):
+                continue
+            used, waited = _scalars(ins.partition(" ")[2]), 0
+            reads += bool(used)
+            for before in reversed(body[max(0, i - 5):i]):
+                op, _, args = before.partition(" ")
+                if op.startswith(("v_readfirstlane", "v_readlane", "v_cmp")) and _scalars(args.split(",")[0]) & used:
+                    bad.append((name, before, ins))
+                waited += int(args, 0) + 1 if op == "s_nop" else 1
+                if waited >= 5:
+                    break
+    assert reads > 10000 and not bad, (reads, len(bad), bad[:3])
 
 
 def test_float_gemm_barriers_wait_for_lds_reads(listings):
